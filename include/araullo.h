@@ -364,12 +364,15 @@ ar_status index_orientations_sparse(ar_context *ctx, const float *images, int64_
  *   k = ((a - L/2), (b - L/2), (c - L/2)) * dk,  dk = 2 k_max / L,
  * over the gathered relative coordinates d_w of ROI r (k in cycles per
  * length unit of the coordinates; the origin a = b = c = L/2 holds N_w).
- * Evaluated as one complex GEMM per ROI on FP32 matrix cores.
+ * Evaluated as one real GEMM per ROI over an octant of the grid, the FP32
+ * factors split into two FP16 parts on the matrix cores with FP32
+ * accumulation.
  *   rel, offsets  gathered CSR (ar_roi_gather)
  *   L             multiple of 32 in [32, 512]
  *   k_max         > 0 (the grid covers [-k_max, k_max - dk] per axis)
  *   amp           device float [n_roi][L][L][L], out
- * AR_EINVAL if n_roi * L^3 / 4096 workgroups exceed 2^31 - 1.  Does not
+ * AR_EINVAL if the launch would exceed 2^31 - 1 workgroups (n_roi times
+ * (L/32)^2 ceil(L/64) + 3 ceil(L/64)^2 / 8 + 3 L / 32, about).  Does not
  * synchronise.
  */
 ar_status ar_fsp_amplitudes(ar_context *ctx, const float *rel, const int64_t *offsets, int64_t n_roi,
