@@ -326,5 +326,179 @@ __device__ __forceinline__ int eq1_bin(float vx, float vy, float vz, float dx, f
     return (int)__builtin_amdgcn_fmed3f(t, 0.0f, last);
 }
 
+// ------------------------------------------------- windows on matrix cores
+// When the windows span at most 32 bins, only those bins of the spectrum are
+// evaluated, as a product on the matrix cores instead of an FFT.  With
+// n = N2 n1 + n2 (n1 < 64, N2 = NB / 64) and m = n1 + 1/2,
+//   X_k = sum_n2 e^(-2 pi i k (n2 - N2 / 2) / NB) S[n2][k],
+//   S[n2][k] = sum_n1 h[N2 n1 + n2] e^(-2 pi i k m / 64).
+// m and 64 - m (n1 and 63 - n1) have the same cosine and opposite sines, so
+// the sums run over 32 pairs, cosines of h + h' and sines of h - h'.  The
+// inner sums of D = 32 / N2 directions are one 32-row product with the 32 x
+// 32 tables of cosines and sines (v_mfma_f32_32x32x16_f16; row d N2 + n2,
+// column k - kmin), the outer sum of N2 terms is FP32 on the vector unit.
+//
+// Exactness: a count c < 2048 is the FP16 number of bit pattern c, c 2^-24, so
+// a pair of histogram words becomes a pair of A operands by packing, an
+// integer addition of the partners' pair, and one v_pk_mul_f16 by 2^10
+// (h + h') or v_pk_fma_f16 (h - h' = 2 h - (h + h')).  (The product makes it a
+// normal number: the matrix cores keep subnormals but align them as if they
+// were 2^-14, which cost the accumulator up to 10 of its bits, 3e-5 of |X_k|
+// for one atom.)  The table entries are split into two FP16 parts (22 bits);
+// products are exact and accumulate in FP32; 2^14 goes into the outer factors.
+// ROIs of at least 2048 atoms take their counts 10 bits at a time (up to
+// 2^29).
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <int NB> struct BinPlan {
+    static constexpr int N2 = NB / 64;          // rows per direction
+    static constexpr int D = 32 / N2;           // directions per wavefront pass
+    static constexpr int STRIDE = NB + N2;      // words from one histogram to the next: the rows read
+                                                // together (d, n2) then lie in 32 different banks
+    static constexpr int WORDS = D * STRIDE;    // histograms of one wavefront
+    static constexpr int TW = N2 == 4 ? 4 : N2 / 2;   // outer factors per lane
+    static_assert(NB >= 256 && NB <= 2048, "8, 4, 2 or 1 directions per pass");
+};
+
+// Per-lane tables, loaded once per kernel; k = the lane's bin (lane % 32).
+template <int NB> struct BinTables {
+    using P = BinPlan<NB>;
+    f16x8 c_hi[2], c_lo[2], s_hi[2], s_lo[2];   // B operands of the two slices of 16 pairs: cos, -sin of 2 pi k m / 64
+    float2 tw[P::TW];                            // 2^14 e^(-2 pi i k (n2 - N2 / 2) / NB), n2 of the lane's rows
+    int rd;                                      // row reduction: bin read by this lane
+
+    __device__ __forceinline__ void load(const float2 *__restrict__ Wg, const WindowSet &ws, int lane)
+    {
+        const int k = min(ws.kmin + (lane & 31), ws.kmax), h = lane >> 5;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float2 w = Wg[(k * (2 * (16 * s + 8 * h + e) + 1) * (P::N2 / 2)) & (NB - 1)];
+                c_hi[s][e] = (_Float16)w.x;
+                c_lo[s][e] = (_Float16)(w.x - (float)c_hi[s][e]);
+                s_hi[s][e] = (_Float16)w.y;
+                s_lo[s][e] = (_Float16)(w.y - (float)s_hi[s][e]);
+            }
+        // D layout: value i of lane l is row 8 (i / 4) + 4 (l / 32) + i % 4
+#pragma unroll
+        for (int i = 0; i < P::TW; ++i) {
+            const int n2 = P::N2 == 4 ? i : 8 * (i >> 2) + 4 * h + (i & 3);
+            const float2 w = Wg[(k * (n2 - P::N2 / 2)) & (NB - 1)];
+            tw[i] = make_float2(w.x * 16384.0f, w.y * 16384.0f);
+        }
+        rd = 0;
+        const int w = lane >> 4, i = lane & 15;
+        for (int u = 0; u < ws.n && u < 4; ++u)
+            if (w == u) rd = ws.lo[u] - ws.kmin + min(i, ws.hi[u] - ws.lo[u]);
+    }
+};
+
+// A operands of 8 pairs (c[e], p[e]) of at most 2047 counts together, in
+// units of 2^-14: their sums and differences.
+__device__ __forceinline__ void pair_operands(const uint32_t (&c)[8], const uint32_t (&p)[8], f16x8 &sum, f16x8 &diff)
+{
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const uint32_t x = c[e] | (c[e + 1] << 16), y = p[e] | (p[e + 1] << 16);
+        const f16x2 s = __builtin_bit_cast(f16x2, x + y) * (_Float16)1024.0f;
+        const f16x2 d = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, x), f16x2{(_Float16)2048.0f, (_Float16)2048.0f}, -s);
+        sum[e] = s.x;
+        sum[e + 1] = s.y;
+        diff[e] = d.x;
+        diff[e + 1] = d.y;
+    }
+}
+
+// |X_k| of the wavefront's D histograms: amp[j] is bin lane % 32 of direction
+// 2 j + lane / 32 (D = 1: of the one direction in both halves).  `hist` is the
+// lane's row of its histogram, h its half (lane / 32).
+template <int NB>
+__device__ __forceinline__ void bin_amplitudes(const int *hist, int h, const BinTables<NB> &t, bool large,
+                                               float (&amp)[(BinPlan<NB>::D + 1) / 2])
+{
+    using P = BinPlan<NB>;
+    f32x16 C, S;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) C[i] = S[i] = 0.f;
+    auto product = [&](int s, f16x8 sum, f16x8 diff) {
+        C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sum, t.c_lo[s], C, 0, 0, 0);
+        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(diff, t.s_lo[s], S, 0, 0, 0);
+        C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sum, t.c_hi[s], C, 0, 0, 0);
+        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(diff, t.s_hi[s], S, 0, 0, 0);
+    };
+    const int *up = hist + 8 * h * P::N2, *down = hist + (63 - 8 * h) * P::N2;   // n1 and 63 - n1
+    // pairs past 2047 counts (possible only in ROIs of that many atoms)
+    uint32_t any = 0;
+    if (large) {
+#pragma unroll 4
+        for (int i = 0; i < 24; ++i)
+            if (!(i & 8)) any |= ((uint32_t)up[i * P::N2] + (uint32_t)down[-i * P::N2]) >> 11;
+    }
+    if (!__any(any != 0)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            uint32_t c[8], p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                c[e] = (uint32_t)up[(16 * s + e) * P::N2];
+                p[e] = (uint32_t)down[-(16 * s + e) * P::N2];
+            }
+            f16x8 sum, diff;
+            pair_operands(c, p, sum, diff);
+            product(s, sum, diff);
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll 1
+            for (int sh = 0; sh < 30; sh += 10) {
+                uint32_t c[8], p[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    c[e] = ((uint32_t)up[(16 * s + e) * P::N2] >> sh) & 1023u;
+                    p[e] = ((uint32_t)down[-(16 * s + e) * P::N2] >> sh) & 1023u;
+                }
+                f16x8 sum, diff;
+                pair_operands(c, p, sum, diff);
+                // 2^sh in two factors: 2^20 is no FP16 number
+                const _Float16 f = (_Float16)(sh > 0 ? 1024.0f : 1.0f), g = (_Float16)(sh > 10 ? 1024.0f : 1.0f);
+                product(s, sum * f * g, diff * f * g);
+            }
+    }
+    // sum of the direction's rows in this lane, values i0 .. i0 + TW - 1
+    auto rows = [&](int i0) {
+        float2 x[4];   // four partial sums, as short as the terms allow
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = cmul(make_float2(C[i0 + i], S[i0 + i]), t.tw[i]);
+#pragma unroll
+        for (int i = 4; i < P::TW; ++i) x[i & 3] = cmac(x[i & 3], make_float2(C[i0 + i], S[i0 + i]), t.tw[i]);
+        return cadd(cadd(x[0], x[1]), cadd(x[2], x[3]));
+    };
+#pragma unroll
+    for (int j = 0; j < (P::D + 1) / 2; ++j) {
+        float2 x;
+        if constexpr (P::N2 == 4) {
+            x = rows(4 * j);   // rows 8 j + 4 (lane / 32) .. + 3: one direction per half
+        } else if constexpr (P::D == 1) {
+            x = rows(0);
+            x.x += __shfl_xor(x.x, 32);
+            x.y += __shfl_xor(x.y, 32);
+        } else {
+            // both halves hold half the rows of directions 2 j and 2 j + 1:
+            // swap so that each half sums one direction
+            const float2 a = rows(2 * j * P::TW), b = rows((2 * j + 1) * P::TW);
+            const auto re = __builtin_amdgcn_permlane32_swap(__float_as_uint(a.x), __float_as_uint(b.x), false, false);
+            const auto im = __builtin_amdgcn_permlane32_swap(__float_as_uint(a.y), __float_as_uint(b.y), false, false);
+            x = make_float2(__uint_as_float(re[0]) + __uint_as_float(re[1]),
+                            __uint_as_float(im[0]) + __uint_as_float(im[1]));
+        }
+        amp[j] = sqrtf(fmaf(x.x, x.x, x.y * x.y));
+    }
+}
+
 }  // namespace sig
 }  // namespace ar

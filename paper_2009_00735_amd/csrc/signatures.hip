@@ -15,6 +15,10 @@
 // |X_k|.  Window maxima are a 16-lane DPP reduction.  No workgroup barrier is
 // needed for a ROI whose atoms fit the stage.
 //
+// Windows within 32 bins (every signature in use) take the window products on
+// the matrix cores instead of the FFT (bin_amplitudes); the FFT form above
+// serves wider windows, 4096 bins and the whole spectra of araullo_sdm.
+//
 // Two launch forms share that per-direction code:
 //   plain       one workgroup per (ROI, direction tile), hardware dispatch;
 //   persistent  CU-filling grid whose workgroups pull (ROI, direction chunk)
@@ -101,13 +105,20 @@ template <int LOGNB> struct LaneConsts {
 // and the LDS atomics of one instruction then serialise.  The remaining
 // n - 64 q atoms (fewer than 64) keep their order at slots 64 q .. n - 1.
 // The histogram is a sum of integer counts, the same in any order.
-__device__ __forceinline__ void stage_atoms(float4 *xs, const float4 *__restrict__ rel, int64_t first, int n)
+// A = float4 (FFT form) or Atom3.
+struct Atom3 {
+    float x, y, z;
+};
+template <typename A>
+__device__ __forceinline__ void stage_atoms(A *xs, const float4 *__restrict__ rel, int64_t first, int n)
 {
     const int q = n / kWave;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int l = q > 0 ? i / q : 0;
         const int slot = i < q * kWave ? (i - l * q) * kWave + l : i;
-        xs[slot] = rel[first + i];
+        const float4 a = rel[first + i];
+        if constexpr (sizeof(A) == sizeof(float4)) xs[slot] = a;
+        else xs[slot] = A{a.x, a.y, a.z};
     }
 }
 
@@ -332,6 +343,226 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, 8))) 
     }
 }
 
+// ------------------------------------- the same launch forms, matrix cores
+// Windows within 32 bins and up to 2048 bins (bin_amplitudes): a wavefront
+// bins D = 2048 / NB directions at a time, so an atom is read from the stage
+// once per D directions, and no FFT passes go through LDS.
+//
+// Bound: the FFT form kept the LDS busy 81 % of the time at 1024 bins (471
+// cycles per ROI-direction, 115 of them conflicts of the atomics).  Here the
+// histograms are written and read once: about 280 cycles, the atomics most of
+// it; 249 measured, the LDS busy 77 % of the time, with the vector unit (246
+// instructions per ROI-direction, 393 before) close behind.  200 ROIs of 1006
+// atoms and 10242 directions: 1.21 ms, FFT form 2.04; 500 clipped ROIs in the
+// persistent form 3.14 ms, 5.34.  Three workgroups per CU (12-byte atoms in
+// the stage, 168 registers): two cost 9 %, four (spilling) 10 %.  Reading the
+// next atoms ahead of the atomics changed nothing.
+template <int NB> constexpr size_t wave_bytes_mm() { return ((size_t)BinPlan<NB>::WORDS + kWave) * 4; }
+size_t lds_mm(int nbins, int cap)
+{
+    const int n2 = nbins / 64, words = 32 / n2 * (nbins + n2);
+    return (size_t)cap * sizeof(Atom3) + (size_t)kWaves * ((size_t)words + kWave) * 4 + 16;
+}
+
+// Directions of one pass: unit vectors, wave-uniform.
+template <int D> struct Dirs {
+    float x[D], y[D], z[D];
+    __device__ __forceinline__ void load(const float *__restrict__ dirs, int v, int v1)
+    {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int u = min(v + d, v1 - 1);   // past the end: the last one again, not written
+            x[d] = dirs[3 * u];
+            y[d] = dirs[3 * u + 1];
+            z[d] = dirs[3 * u + 2];
+        }
+    }
+};
+
+// Eq. (1) of n staged atoms for the pass's directions; as bin_staged, a few
+// slots at a time with the atomics back to back.
+template <int NB>
+__device__ __forceinline__ void bin_staged_mm(const Atom3 *xs, int n, const Dirs<BinPlan<NB>::D> &v, BinConsts bc,
+                                              int *hist, int lane)
+{
+    using P = BinPlan<NB>;
+    constexpr float last = (float)(NB - 1);
+    constexpr int SLOTS = P::D >= 4 ? 2 : 4;
+    const Atom3 *p = xs + lane;
+    int g = 0;
+    for (; (g + SLOTS) * kWave <= n; g += SLOTS, p += SLOTS * kWave) {
+        int b[SLOTS][P::D];
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i) {
+            const Atom3 a = p[i * kWave];
+#pragma unroll
+            for (int d = 0; d < P::D; ++d)
+                b[i][d] = eq1_bin(v.x[d], v.y[d], v.z[d], a.x, a.y, a.z, bc.shift, bc.scale, last);
+        }
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i)
+#pragma unroll
+            for (int d = 0; d < P::D; ++d) atomicAdd(&hist[d * P::STRIDE + b[i][d]], 1);
+    }
+    for (; g * kWave < n; ++g, p += kWave)
+        if (g * kWave + lane < n) {
+            const Atom3 a = *p;
+#pragma unroll
+            for (int d = 0; d < P::D; ++d)
+                atomicAdd(&hist[d * P::STRIDE + eq1_bin(v.x[d], v.y[d], v.z[d], a.x, a.y, a.z, bc.shift, bc.scale, last)],
+                          1);
+        }
+}
+
+template <int NB> __device__ __forceinline__ void zero_hist_mm(int *hist, int lane)
+{
+    constexpr int N4 = BinPlan<NB>::WORDS / 4;
+#pragma unroll
+    for (int i = 0; i < (N4 + kWave - 1) / kWave; ++i)
+        if (N4 % kWave == 0 || i * kWave + lane < N4) reinterpret_cast<int4 *>(hist)[i * kWave + lane] = make_int4(0, 0, 0, 0);
+    wave_lds_sync();
+}
+
+// Window maxima of the finished histograms of directions v .. v + D - 1 (those
+// below v1) of ROI r.
+template <int NB>
+__device__ __forceinline__ void finish_pass(const int *hist, float *scratch, const BinTables<NB> &t, const WindowSet &ws,
+                                            int lane, bool large, int64_t r, int v, int v1, int n_dir,
+                                            float *__restrict__ images)
+{
+    using P = BinPlan<NB>;
+    wave_lds_sync();
+    float amp[(P::D + 1) / 2];
+    const int row = lane & 31, h = lane >> 5;
+    bin_amplitudes<NB>(hist + (row / P::N2) * P::STRIDE + row % P::N2, h, t, large, amp);
+    float *out = images + ((size_t)r * ws.n + (lane >> 4)) * n_dir;
+#pragma unroll
+    for (int j = 0; j < (P::D + 1) / 2; ++j) {
+        wave_lds_sync();
+        scratch[lane] = amp[j];
+        wave_lds_sync();
+        // row lane / 16: window lane / 16 of direction 2 j, then of 2 j + 1
+        const float m0 = row_max16(scratch[t.rd]);
+        const float m1 = P::D == 1 ? 0.f : row_max16(scratch[32 + t.rd]);
+        const int d = v + 2 * j + (lane & 1);
+        if ((lane & 15) < (P::D == 1 ? 1 : 2) && (lane >> 4) < ws.n && d < v1) out[d] = (lane & 1) ? m1 : m0;
+    }
+}
+
+// Directions [v0, v1) of ROI r by the wavefronts of the workgroup, as
+// process_item.
+template <int LOGNB>
+__device__ __forceinline__ void process_item_mm(const float4 *__restrict__ rel, int64_t off0, int nw, int64_t r, int v0,
+                                                int v1, const float *__restrict__ dirs, int n_dir, BinConsts bc,
+                                                const WindowSet &ws, const BinTables<(1 << LOGNB)> &t, Atom3 *xs, int cap,
+                                                int *hist, int wave, int lane, float *__restrict__ images)
+{
+    constexpr int NB = 1 << LOGNB;
+    constexpr int D = BinPlan<NB>::D;
+    float *scratch = reinterpret_cast<float *>(hist + BinPlan<NB>::WORDS);
+    const bool large = nw > 2047;
+    if (nw <= cap) {
+        for (int v = v0 + wave * D; v < v1; v += kWaves * D) {
+            Dirs<D> u;
+            u.load(dirs, v, v1);
+            zero_hist_mm<NB>(hist, lane);
+            bin_staged_mm<NB>(xs, nw, u, bc, hist, lane);
+            finish_pass<NB>(hist, scratch, t, ws, lane, large, r, v, v1, n_dir, images);
+        }
+        return;
+    }
+    for (int vr = v0; vr < v1; vr += kWaves * D) {
+        const int v = vr + wave * D;
+        const bool active = v < v1;
+        Dirs<D> u;
+        if (active) {
+            u.load(dirs, v, v1);
+            zero_hist_mm<NB>(hist, lane);
+        }
+        for (int c0 = 0; c0 < nw; c0 += cap) {
+            const int n = min(cap, nw - c0);
+            __syncthreads();
+            stage_atoms(xs, rel, off0 + c0, n);
+            __syncthreads();
+            if (active) bin_staged_mm<NB>(xs, n, u, bc, hist, lane);
+        }
+        if (active) finish_pass<NB>(hist, scratch, t, ws, lane, large, r, v, v1, n_dir, images);
+    }
+}
+
+template <int LOGNB>
+__global__ __launch_bounds__(256, 3) void k_signatures_plain_mm(const float4 *__restrict__ rel,
+                                                             const int64_t *__restrict__ offsets,
+                                                             const float *__restrict__ dirs, int n_dir,
+                                                             int dirs_per_block, int n_tiles,
+                                                             const float2 *__restrict__ Wg, BinConsts bc, WindowSet ws,
+                                                             int cap, float *__restrict__ images, int32_t *, float *)
+{
+    constexpr int NB = 1 << LOGNB;
+    extern __shared__ __align__(16) unsigned char smem[];
+    Atom3 *xs = reinterpret_cast<Atom3 *>(smem);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int *hist = reinterpret_cast<int *>(smem + (size_t)cap * sizeof(Atom3) + (size_t)wave * wave_bytes_mm<NB>());
+    const int64_t r = (int64_t)blockIdx.x / n_tiles;
+    const int tile = (int)((int64_t)blockIdx.x - r * n_tiles);
+    const int64_t off0 = offsets[r];
+    const int nw = (int)(offsets[r + 1] - off0);
+    if (nw <= cap) stage_atoms(xs, rel, off0, nw);
+    BinTables<NB> t;
+    t.load(Wg, ws, lane);
+    const int v0 = tile * dirs_per_block;
+    const int v1 = min(v0 + dirs_per_block, n_dir);
+    __syncthreads();
+    process_item_mm<LOGNB>(rel, off0, nw, r, v0, v1, dirs, n_dir, bc, ws, t, xs, cap, hist, wave, lane, images);
+}
+
+template <int LOGNB>
+__global__ __launch_bounds__(256, 3) void k_signatures_persistent_mm(
+    const float4 *__restrict__ rel, const int64_t *__restrict__ offsets, const int32_t *__restrict__ order,
+    int64_t n_items, int chunks, int dpi, const float *__restrict__ dirs, int n_dir, const float2 *__restrict__ Wg,
+    BinConsts bc, WindowSet ws, int cap, float *__restrict__ images, unsigned long long *__restrict__ counter)
+{
+    constexpr int NB = 1 << LOGNB;
+    extern __shared__ __align__(16) unsigned char smem[];
+    Atom3 *xs = reinterpret_cast<Atom3 *>(smem);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int *hist = reinterpret_cast<int *>(smem + (size_t)cap * sizeof(Atom3) + (size_t)wave * wave_bytes_mm<NB>());
+    // the item slot lies after the stage and the wave buffers, as in the FFT form
+    unsigned long long *slot =
+        reinterpret_cast<unsigned long long *>(smem + (size_t)cap * sizeof(Atom3) + (size_t)kWaves * wave_bytes_mm<NB>());
+    BinTables<NB> t;
+    t.load(Wg, ws, lane);
+    int64_t cur = -1;
+    for (;;) {
+        if (threadIdx.x == 0) *slot = atomicAdd(counter, 1ull);
+        __syncthreads();
+        const unsigned long long it = *slot;
+        const int64_t item = (int64_t)(__builtin_amdgcn_readfirstlane((unsigned)it) |
+                                       ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(it >> 32)) << 32));
+        if ((unsigned long long)item >= (unsigned long long)n_items) break;
+        const int64_t r = order[item / chunks];
+        const int c = (int)(item % chunks);
+        const int64_t off0 = offsets[r];
+        const int nw = (int)(offsets[r + 1] - off0);
+        if (nw <= cap && r != cur) {
+            stage_atoms(xs, rel, off0, nw);
+            __syncthreads();
+        }
+        cur = nw <= cap ? r : -1;
+        const int v0 = c * dpi, v1 = min(v0 + dpi, n_dir);
+        process_item_mm<LOGNB>(rel, off0, nw, r, v0, v1, dirs, n_dir, bc, ws, t, xs, cap, hist, wave, lane, images);
+        __syncthreads();
+    }
+}
+
+// The matrix-core form takes windows within 32 bins, at most four of at most
+// 16 bins each, and histograms up to 2048 bins; 4096 bins would need two row
+// tiles and 64 registers of outer factors, wider windows more columns, and
+// araullo_sdm the whole spectrum: those take the FFT.
+bool use_mm(int nbins, const WindowSet &ws) { return ws.rows == 2 && nbins <= 2048; }
+
 __global__ void k_zero_counter(unsigned long long *c) { *c = 0ull; }
 
 // ------------------------------------------------------------ dispatch
@@ -348,6 +579,26 @@ template <bool DEBUG> PlainFn plain_kernel(int lognb)
     case 10: return k_signatures_plain<10, DEBUG>;
     case 11: return k_signatures_plain<11, DEBUG>;
     default: return k_signatures_plain<12, DEBUG>;
+    }
+}
+
+PlainFn plain_kernel_mm(int lognb)
+{
+    switch (lognb) {
+    case 8: return k_signatures_plain_mm<8>;
+    case 9: return k_signatures_plain_mm<9>;
+    case 10: return k_signatures_plain_mm<10>;
+    default: return k_signatures_plain_mm<11>;
+    }
+}
+
+PersFn pers_kernel_mm(int lognb)
+{
+    switch (lognb) {
+    case 8: return k_signatures_persistent_mm<8>;
+    case 9: return k_signatures_persistent_mm<9>;
+    case 10: return k_signatures_persistent_mm<10>;
+    default: return k_signatures_persistent_mm<11>;
     }
 }
 
@@ -396,18 +647,31 @@ ar_status check_sig_args(ar_context *ctx, int64_t n_roi, float radius, const flo
 
 ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets, int64_t n_roi, float radius,
                        const float *directions, int32_t n_dir, int32_t nbins, const WindowSet &ws, float *images,
-                       int32_t *hist, float *amp, int cap, int dirs_per_block, hipStream_t stream)
+                       int32_t *hist, float *amp, int cap, hipStream_t stream)
 {
     const float2 *W = nullptr;
     AR_TRY(ctx->twiddle_table(nbins, &W));
     const BinConsts bc = bin_consts(radius, nbins);
     const bool debug = hist != nullptr || amp != nullptr;
+    const bool mm = !debug && sig::use_mm(nbins, ws);
+    // Directions per workgroup: 256, so that staging the ROI and the lane
+    // tables (2-3 us) is a few percent, halved while the call would not fill
+    // the chip eight times over, down to one pass of every wavefront.  One
+    // ROI of 642 directions and 256 bins: 21 workgroups instead of 3, 7 us
+    // instead of 83.
+    int dirs_per_block = debug ? 64 : 256;
+    const int least = mm ? sig::kWaves * (2048 / nbins) : 4 * sig::kWaves;
+    while (dirs_per_block > least &&
+           n_roi * (int64_t)((n_dir + dirs_per_block - 1) / dirs_per_block) < 8 * 3 * (int64_t)ctx->cu_count)
+        dirs_per_block /= 2;
     const int n_tiles = (n_dir + dirs_per_block - 1) / dirs_per_block;
     const int64_t blocks = n_roi * (int64_t)n_tiles;
     AR_CHECK(blocks < (int64_t)INT32_MAX, "too many workgroups (%lld)", (long long)blocks);
     AR_CHECK(cap % sig::kStageMult == 0 && cap >= sig::kStageMult && cap <= sig::kStageMax, "bad stage size %d", cap);
-    const size_t lds = sig::lds_for(nbins, cap);
-    sig::PlainFn fn = debug ? sig::plain_kernel<true>(log2i(nbins)) : sig::plain_kernel<false>(log2i(nbins));
+    const size_t lds = mm ? sig::lds_mm(nbins, cap) : sig::lds_for(nbins, cap);
+    sig::PlainFn fn = debug ? sig::plain_kernel<true>(log2i(nbins))
+                      : mm  ? sig::plain_kernel_mm(log2i(nbins))
+                            : sig::plain_kernel<false>(log2i(nbins));
     AR_TRY(sig::allow_lds(fn, lds));
     fn<<<(unsigned)blocks, sig::kWaves * 64, lds, stream>>>((const float4 *)rel, offsets, directions, n_dir,
                                                            dirs_per_block, n_tiles, W, bc, ws, cap, images, hist,
@@ -482,11 +746,12 @@ static ar_status plan_launch(ar_plan *p, const float *rel, const int64_t *offset
     const BinConsts bc = bin_consts(radius, p->nbins);
     const int chunks = (p->n_dir + p->dpi - 1) / p->dpi;
     const int64_t n_items = n_roi * (int64_t)chunks;
-    const size_t lds = sig::lds_for(p->nbins, p->cap);
+    const bool mm = sig::use_mm(p->nbins, ws);
+    const size_t lds = mm ? sig::lds_mm(p->nbins, p->cap) : sig::lds_for(p->nbins, p->cap);
     const int blocks = ctx->cu_count * p->blocks_per_cu;
     sig::k_zero_counter<<<1, 1, 0, stream>>>(p->counter.as<unsigned long long>());
     AR_HIP(hipGetLastError());
-    sig::PersFn fn = sig::pers_kernel(log2i(p->nbins), p->min_waves);
+    sig::PersFn fn = mm ? sig::pers_kernel_mm(log2i(p->nbins)) : sig::pers_kernel(log2i(p->nbins), p->min_waves);
     AR_TRY(sig::allow_lds(fn, lds));
     fn<<<blocks, sig::kWaves * 64, lds, stream>>>((const float4 *)rel, offsets, p->order.as<int32_t>(), n_items,
                                                  chunks, p->dpi, directions, p->n_dir, W, bc, ws, p->cap, images,
@@ -509,7 +774,7 @@ ar_status araullo_signatures_csr(ar_context *ctx, const float *rel, const int64_
     AR_TRY(ar::make_windows(windows, n_win, nbins, &ws));
     AR_HIP(hipSetDevice(ctx->device));
     return ar::launch_plain(ctx, rel, offsets, n_roi, radius, directions, n_dir, nbins, ws, images, nullptr, nullptr,
-                            1024, 256, (hipStream_t)stream);
+                            1024, (hipStream_t)stream);
 }
 
 static ar_status gather_into_ctx(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
@@ -553,7 +818,7 @@ ar_status araullo_signatures(ar_context *ctx, const float *positions, int64_t n_
         AR_HIP(hipStreamSynchronize(s));
     }
     return ar::launch_plain(ctx, ctx->s_rel.as<float>(), ctx->g_offsets.as<int64_t>(), n_roi, radius, directions,
-                            n_dir, nbins, ws, images, nullptr, nullptr, cap, 256, s);
+                            n_dir, nbins, ws, images, nullptr, nullptr, cap, s);
 }
 
 ar_status araullo_signatures_typed(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
@@ -587,7 +852,7 @@ ar_status araullo_signatures_typed(ar_context *ctx, const float *positions, cons
             for (int64_t r = 0; r < n_roi; ++r) cnt[(size_t)r * n_ch + c] = (int32_t)(off[r + 1] - off[r]);
         AR_TRY(ar::launch_plain(ctx, ctx->s_rel.as<float>(), ctx->g_offsets.as<int64_t>(), n_roi, radius, directions,
                                 n_dir, nbins, ws, ctx->s_typed.as<float>(), nullptr, nullptr, ar::sig::stage_for(big),
-                                256, s));
+                                s));
         // channel c of every ROI: rows of img_row floats at a pitch of n_ch rows
         AR_HIP(hipMemcpy2DAsync(images + (size_t)c * img_row, sizeof(float) * img_row * n_ch, ctx->s_typed.ptr,
                                 sizeof(float) * img_row, sizeof(float) * img_row, (size_t)n_roi,
@@ -614,7 +879,7 @@ ar_status araullo_sdm(ar_context *ctx, const float *positions, int64_t n_atoms, 
     ar::WindowSet ws;
     memset(&ws, 0, sizeof(ws));
     return ar::launch_plain(ctx, ctx->s_rel.as<float>(), ctx->g_offsets.as<int64_t>(), n_roi, radius, directions,
-                            n_dir, nbins, ws, nullptr, hist, amp, 1024, 64, s);
+                            n_dir, nbins, ws, nullptr, hist, amp, 1024, s);
 }
 
 ar_status ar_signature_plan_create(ar_context *ctx, int64_t max_roi, int64_t max_total, int32_t n_dir, int32_t nbins,
@@ -682,7 +947,7 @@ ar_status ar_signature_plan_tune(ar_plan *p, const float *rel, const int64_t *of
     const int dpis[] = {16, 32, 64, 128};
     const int bpcs[] = {2, 3, 4, 6};
     std::vector<int> occs = {1};
-    if (p->nbins <= 1024) occs.push_back(4);
+    if (p->nbins <= 1024 && !ar::sig::use_mm(p->nbins, ws)) occs.push_back(4);   // the matrix-core form has one
     // stage sizes: one that holds the largest ROI, and smaller ones that let
     // more workgroups share a compute unit (larger ROIs are then streamed)
     std::vector<int> caps = {ar::sig::stage_for(p->big)};
