@@ -74,7 +74,9 @@ struct ar_context {
     int cu_count = 0;
     int lds_per_block = 0;
     // gather workspace
-    ar::DeviceBuffer g_keys, g_vals, g_counts32, g_cell_start, g_sorted, g_counts, g_temp, g_bbox, g_offsets;
+    ar::DeviceBuffer g_keys, g_slot, g_vals, g_counts32, g_cell_start, g_sorted, g_counts, g_rows, g_temp, g_offsets;
+    // host memory that kernels write sizes the host waits for into (kHostBytes), and its device address
+    void *host = nullptr, *host_dev = nullptr;
     // gathered CSR used by the position-taking signature entry points
     ar::DeviceBuffer s_rel;
     // one channel's images in the typed-signature entry point
@@ -94,6 +96,7 @@ struct ar_context {
     // twiddle tables exp(-2 pi i j / nbins), j < nbins, per nbins
     std::map<int, std::unique_ptr<ar::DeviceBuffer>> twiddles;
     ar_status twiddle_table(int nbins, const float2 **out);
+    ~ar_context();
 };
 
 struct ar_library {
@@ -117,6 +120,34 @@ namespace ar {
 ar_status gather_csr(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
                      const float *centres, int64_t n_roi, float radius, uint64_t type_mask, int64_t *offsets,
                      float *rel, int64_t cap, int64_t *total, hipStream_t stream);
+// The rows of one gather: ROI r at rel[offsets[stride r] .. offsets[stride r +
+// 1]), and the largest ROI (or a bound of it).
+struct GatheredRois {
+    const float *rel;
+    const int64_t *offsets;
+    int stride;
+    int64_t big;
+};
+// A reference to a callable (const GatheredRois &, int mask) -> ar_status.
+struct RoiUse {
+    void *self;
+    ar_status (*call)(void *, const GatheredRois &, int);
+    template <class F>
+    RoiUse(F &f) : self(&f), call([](void *p, const GatheredRois &g, int c) { return (*static_cast<F *>(p))(g, c); })
+    {
+    }
+    ar_status operator()(const GatheredRois &g, int c) const { return call(self, g, c); }
+};
+// Gather once per type mask into the context's buffers, the atoms sorted once
+// for all of them, and hand each gather to `use`, which queues the work that
+// reads it.  counts: device int32 [n_roi][n_masks] or NULL, out.  want_big:
+// `big` must be the largest ROI, not a bound (may wait for it).  The rows'
+// order within a ROI is unspecified.
+ar_status gather_rois(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
+                      const float *centres, int64_t n_roi, float radius, const uint64_t *type_masks, int n_masks,
+                      int32_t *counts, bool want_big, hipStream_t stream,
+                      RoiUse use);
+constexpr size_t kHostBytes = 256;
 struct MeshCells;
 // cube-map nearest-node candidate lists of `dirs` in ctx->m_cells (mesh.hip)
 ar_status build_mesh_cells(ar_context *ctx, const float *dirs, int n_dir, hipStream_t stream, MeshCells &mc);

@@ -93,6 +93,11 @@ ar_status make_windows(const int32_t *windows, int32_t n_win, int32_t nbins, Win
 
 }  // namespace ar
 
+ar_context::~ar_context()
+{
+    if (host) (void)hipHostFree(host);
+}
+
 ar_status ar_context::twiddle_table(int nbins, const float2 **out)
 {
     auto it = twiddles.find(nbins);
@@ -134,6 +139,17 @@ ar_status ar_context_create(int device, ar_context **out)
     c->device = device;
     c->cu_count = prop.multiProcessorCount;
     c->lds_per_block = (int)prop.sharedMemPerBlock;
+    if (hipHostMalloc(&c->host, ar::kHostBytes, hipHostMallocMapped) != hipSuccess) {
+        c->host = nullptr;
+        (void)hipGetLastError();
+        delete c;
+        return ar::fail(AR_ENOMEM, "host memory allocation failed");
+    }
+    if (hipHostGetDevicePointer(&c->host_dev, c->host, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        delete c;
+        return ar::fail(AR_EDEVICE, "no device address for host memory");
+    }
     *out = c;
     return AR_OK;
 }

@@ -269,8 +269,8 @@ __device__ __forceinline__ void process_item(const float4 *__restrict__ rel, int
 // ---------------------------------------------------------------- plain form
 template <int LOGNB, bool DEBUG>
 __global__ __launch_bounds__(256) void k_signatures_plain(
-    const float4 *__restrict__ rel, const int64_t *__restrict__ offsets, const float *__restrict__ dirs, int n_dir,
-    int dirs_per_block, int n_tiles, const float2 *__restrict__ Wg, BinConsts bc, WindowSet ws, int cap,
+    const float4 *__restrict__ rel, const int64_t *__restrict__ offsets, int ostride, const float *__restrict__ dirs,
+    int n_dir, int dirs_per_block, int n_tiles, const float2 *__restrict__ Wg, BinConsts bc, WindowSet ws, int cap,
     float *__restrict__ images, int32_t *__restrict__ hist_out, float *__restrict__ amp_out)
 {
     constexpr int NB = 1 << LOGNB;
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(256) void k_signatures_plain(
 
     const int64_t r = (int64_t)blockIdx.x / n_tiles;
     const int tile = (int)((int64_t)blockIdx.x - r * n_tiles);
-    const int64_t off0 = offsets[r];
-    const int nw = (int)(offsets[r + 1] - off0);
+    const int64_t off0 = offsets[r * ostride];
+    const int nw = (int)(offsets[r * ostride + 1] - off0);
     const int v0 = tile * dirs_per_block;
     const int v1 = min(v0 + dirs_per_block, n_dir);
     if (nw <= cap) {
@@ -492,7 +492,7 @@ __device__ __forceinline__ void process_item_mm(const float4 *__restrict__ rel, 
 
 template <int LOGNB>
 __global__ __launch_bounds__(256, 3) void k_signatures_plain_mm(const float4 *__restrict__ rel,
-                                                             const int64_t *__restrict__ offsets,
+                                                             const int64_t *__restrict__ offsets, int ostride,
                                                              const float *__restrict__ dirs, int n_dir,
                                                              int dirs_per_block, int n_tiles,
                                                              const float2 *__restrict__ Wg, BinConsts bc, WindowSet ws,
@@ -506,8 +506,8 @@ __global__ __launch_bounds__(256, 3) void k_signatures_plain_mm(const float4 *__
     int *hist = reinterpret_cast<int *>(smem + (size_t)cap * sizeof(Atom3) + (size_t)wave * wave_bytes_mm<NB>());
     const int64_t r = (int64_t)blockIdx.x / n_tiles;
     const int tile = (int)((int64_t)blockIdx.x - r * n_tiles);
-    const int64_t off0 = offsets[r];
-    const int nw = (int)(offsets[r + 1] - off0);
+    const int64_t off0 = offsets[r * ostride];
+    const int nw = (int)(offsets[r * ostride + 1] - off0);
     if (nw <= cap) stage_atoms(xs, rel, off0, nw);
     BinTables<NB> t;
     t.load(Wg, ws, lane);
@@ -566,7 +566,7 @@ bool use_mm(int nbins, const WindowSet &ws) { return ws.rows == 2 && nbins <= 20
 __global__ void k_zero_counter(unsigned long long *c) { *c = 0ull; }
 
 // ------------------------------------------------------------ dispatch
-using PlainFn = void (*)(const float4 *, const int64_t *, const float *, int, int, int, const float2 *, BinConsts,
+using PlainFn = void (*)(const float4 *, const int64_t *, int, const float *, int, int, int, const float2 *, BinConsts,
                          WindowSet, int, float *, int32_t *, float *);
 using PersFn = void (*)(const float4 *, const int64_t *, const int32_t *, int64_t, int, int, const float *, int,
                         const float2 *, BinConsts, WindowSet, int, float *, unsigned long long *);
@@ -645,7 +645,8 @@ ar_status check_sig_args(ar_context *ctx, int64_t n_roi, float radius, const flo
     return AR_OK;
 }
 
-ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets, int64_t n_roi, float radius,
+// ROI r: rel[offsets[ostride r] .. offsets[ostride r + 1]).
+ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets, int ostride, int64_t n_roi, float radius,
                        const float *directions, int32_t n_dir, int32_t nbins, const WindowSet &ws, float *images,
                        int32_t *hist, float *amp, int cap, hipStream_t stream)
 {
@@ -673,7 +674,7 @@ ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets
                       : mm  ? sig::plain_kernel_mm(log2i(nbins))
                             : sig::plain_kernel<false>(log2i(nbins));
     AR_TRY(sig::allow_lds(fn, lds));
-    fn<<<(unsigned)blocks, sig::kWaves * 64, lds, stream>>>((const float4 *)rel, offsets, directions, n_dir,
+    fn<<<(unsigned)blocks, sig::kWaves * 64, lds, stream>>>((const float4 *)rel, offsets, ostride, directions, n_dir,
                                                            dirs_per_block, n_tiles, W, bc, ws, cap, images, hist,
                                                            amp);
     AR_HIP(hipGetLastError());
@@ -773,22 +774,14 @@ ar_status araullo_signatures_csr(ar_context *ctx, const float *rel, const int64_
     ar::WindowSet ws;
     AR_TRY(ar::make_windows(windows, n_win, nbins, &ws));
     AR_HIP(hipSetDevice(ctx->device));
-    return ar::launch_plain(ctx, rel, offsets, n_roi, radius, directions, n_dir, nbins, ws, images, nullptr, nullptr,
+    return ar::launch_plain(ctx, rel, offsets, 1, n_roi, radius, directions, n_dir, nbins, ws, images, nullptr, nullptr,
                             1024, (hipStream_t)stream);
 }
 
-static ar_status gather_into_ctx(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
-                                 const float *centres, int64_t n_roi, float radius, uint64_t type_mask,
-                                 ar::DeviceBuffer &offs, ar::DeviceBuffer &rel, int64_t *total, hipStream_t stream)
-{
-    AR_TRY(offs.reserve(sizeof(int64_t) * (n_roi + 1)));
-    AR_TRY(ar::gather_csr(ctx, positions, types, n_atoms, centres, n_roi, radius, type_mask, offs.as<int64_t>(),
-                          nullptr, 0, total, stream));
-    AR_TRY(rel.reserve(sizeof(float4) * (*total + 1)));
-    AR_TRY(ar::gather_csr(ctx, positions, types, n_atoms, centres, n_roi, radius, type_mask, offs.as<int64_t>(),
-                          rel.as<float>(), *total, total, stream));
-    return AR_OK;
-}
+// A call of few ROI-directions takes the stage from a bound of the largest ROI
+// instead of waiting for its size: it does not fill the chip, so the LDS of a
+// larger stage costs nothing.
+static bool few_directions(int64_t n_roi, int32_t n_dir) { return n_roi * (int64_t)n_dir <= 65536; }
 
 ar_status araullo_signatures(ar_context *ctx, const float *positions, int64_t n_atoms, const float *centres,
                              int64_t n_roi, float radius, const float *directions, int32_t n_dir, int32_t nbins,
@@ -798,27 +791,14 @@ ar_status araullo_signatures(ar_context *ctx, const float *positions, int64_t n_
     AR_CHECK(images != nullptr, "images is NULL");
     ar::WindowSet ws;
     AR_TRY(ar::make_windows(windows, n_win, nbins, &ws));
-    AR_HIP(hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    int64_t total = 0;
-    AR_TRY(gather_into_ctx(ctx, positions, nullptr, n_atoms, centres, n_roi, radius, ~0ull, ctx->g_offsets,
-                           ctx->s_rel, &total, s));
-    // register chunk sized to the largest ROI (read back once; the gather
-    // already synchronised)
-    std::vector<int64_t> off(n_roi + 1);
-    AR_HIP(hipMemcpyAsync(off.data(), ctx->g_offsets.ptr, sizeof(int64_t) * (n_roi + 1), hipMemcpyDeviceToHost, s));
-    AR_HIP(hipStreamSynchronize(s));
-    int64_t big = 0;
-    for (int64_t r = 0; r < n_roi; ++r) big = std::max(big, off[r + 1] - off[r]);
-    const int cap = ar::sig::stage_for(big);
-    if (roi_counts) {
-        std::vector<int32_t> cnt(n_roi);
-        for (int64_t r = 0; r < n_roi; ++r) cnt[r] = (int32_t)(off[r + 1] - off[r]);
-        AR_HIP(hipMemcpyAsync(roi_counts, cnt.data(), sizeof(int32_t) * n_roi, hipMemcpyHostToDevice, s));
-        AR_HIP(hipStreamSynchronize(s));
-    }
-    return ar::launch_plain(ctx, ctx->s_rel.as<float>(), ctx->g_offsets.as<int64_t>(), n_roi, radius, directions,
-                            n_dir, nbins, ws, images, nullptr, nullptr, cap, s);
+    const uint64_t all = ~0ull;
+    auto use = [&](const ar::GatheredRois &g, int) {
+        return ar::launch_plain(ctx, g.rel, g.offsets, g.stride, n_roi, radius, directions, n_dir, nbins, ws, images,
+                                nullptr, nullptr, ar::sig::stage_for(g.big), s);
+    };
+    return ar::gather_rois(ctx, positions, nullptr, n_atoms, centres, n_roi, radius, &all, 1, roi_counts,
+                           !few_directions(n_roi, n_dir), s, use);
 }
 
 ar_status araullo_signatures_typed(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
@@ -837,32 +817,17 @@ ar_status araullo_signatures_typed(ar_context *ctx, const float *positions, cons
     hipStream_t s = (hipStream_t)stream;
     const size_t img_row = (size_t)n_win * n_dir;   // floats per ROI and channel
     AR_TRY(ctx->s_typed.reserve(sizeof(float) * img_row * n_roi));
-    std::vector<int64_t> off(n_roi + 1);
-    std::vector<int32_t> cnt(roi_counts ? (size_t)n_roi * n_ch : 0);
-    for (int32_t c = 0; c < n_ch; ++c) {
-        int64_t total = 0;
-        AR_TRY(gather_into_ctx(ctx, positions, types, n_atoms, centres, n_roi, radius, type_masks[c], ctx->g_offsets,
-                               ctx->s_rel, &total, s));
-        AR_HIP(hipMemcpyAsync(off.data(), ctx->g_offsets.ptr, sizeof(int64_t) * (n_roi + 1), hipMemcpyDeviceToHost,
-                              s));
-        AR_HIP(hipStreamSynchronize(s));
-        int64_t big = 0;
-        for (int64_t r = 0; r < n_roi; ++r) big = std::max(big, off[r + 1] - off[r]);
-        if (roi_counts)
-            for (int64_t r = 0; r < n_roi; ++r) cnt[(size_t)r * n_ch + c] = (int32_t)(off[r + 1] - off[r]);
-        AR_TRY(ar::launch_plain(ctx, ctx->s_rel.as<float>(), ctx->g_offsets.as<int64_t>(), n_roi, radius, directions,
-                                n_dir, nbins, ws, ctx->s_typed.as<float>(), nullptr, nullptr, ar::sig::stage_for(big),
-                                s));
+    auto use = [&](const ar::GatheredRois &g, int c) -> ar_status {
+        AR_TRY(ar::launch_plain(ctx, g.rel, g.offsets, g.stride, n_roi, radius, directions, n_dir, nbins, ws,
+                                ctx->s_typed.as<float>(), nullptr, nullptr, ar::sig::stage_for(g.big), s));
         // channel c of every ROI: rows of img_row floats at a pitch of n_ch rows
         AR_HIP(hipMemcpy2DAsync(images + (size_t)c * img_row, sizeof(float) * img_row * n_ch, ctx->s_typed.ptr,
                                 sizeof(float) * img_row, sizeof(float) * img_row, (size_t)n_roi,
                                 hipMemcpyDeviceToDevice, s));
-    }
-    if (roi_counts) {
-        AR_HIP(hipMemcpyAsync(roi_counts, cnt.data(), sizeof(int32_t) * cnt.size(), hipMemcpyHostToDevice, s));
-        AR_HIP(hipStreamSynchronize(s));
-    }
-    return AR_OK;
+        return AR_OK;
+    };
+    return ar::gather_rois(ctx, positions, types, n_atoms, centres, n_roi, radius, type_masks, n_ch, roi_counts,
+                           !few_directions(n_roi, n_dir), s, use);
 }
 
 ar_status araullo_sdm(ar_context *ctx, const float *positions, int64_t n_atoms, const float *centres, int64_t n_roi,
@@ -871,15 +836,15 @@ ar_status araullo_sdm(ar_context *ctx, const float *positions, int64_t n_atoms, 
 {
     AR_TRY(ar::check_sig_args(ctx, n_roi, radius, directions, n_dir, nbins));
     AR_CHECK(hist != nullptr && amp != nullptr, "hist and amp must both be given");
-    AR_HIP(hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    int64_t total = 0;
-    AR_TRY(gather_into_ctx(ctx, positions, nullptr, n_atoms, centres, n_roi, radius, ~0ull, ctx->g_offsets,
-                           ctx->s_rel, &total, s));
     ar::WindowSet ws;
     memset(&ws, 0, sizeof(ws));
-    return ar::launch_plain(ctx, ctx->s_rel.as<float>(), ctx->g_offsets.as<int64_t>(), n_roi, radius, directions,
-                            n_dir, nbins, ws, nullptr, hist, amp, 1024, s);
+    const uint64_t all = ~0ull;
+    auto use = [&](const ar::GatheredRois &g, int) {
+        return ar::launch_plain(ctx, g.rel, g.offsets, g.stride, n_roi, radius, directions, n_dir, nbins, ws, nullptr,
+                                hist, amp, 1024, s);
+    };
+    return ar::gather_rois(ctx, positions, nullptr, n_atoms, centres, n_roi, radius, &all, 1, nullptr, false, s, use);
 }
 
 ar_status ar_signature_plan_create(ar_context *ctx, int64_t max_roi, int64_t max_total, int32_t n_dir, int32_t nbins,
