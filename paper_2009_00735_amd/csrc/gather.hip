@@ -101,33 +101,13 @@ __global__ __launch_bounds__(256) void k_cell_scatter(const uint32_t *__restrict
     idx[cell_start[key] + slot[i]] = make_int2((int32_t)i, (int32_t)key);
 }
 
-// Cells hold tens of atoms at the R/2 cell edge of a specimen; the ones past
-// kRankCell (large R) are put back in input order here, one thread per cell by
-// insertion, which is linear on the nearly ordered arrivals where ranking is
-// quadratic.
-constexpr int kRankCell = 512;
-__global__ __launch_bounds__(256) void k_cell_order(const int32_t *__restrict__ cell_start, uint32_t ncells,
-                                                    int2 *__restrict__ idx)
-{
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= (int64_t)ncells) return;
-    const int a0 = cell_start[c], a1 = cell_start[c + 1];
-    if (a1 - a0 <= kRankCell) return;
-    for (int a = a0 + 1; a < a1; ++a) {
-        const int2 v = idx[a];
-        int b = a - 1;
-        while (b >= a0 && idx[b].x > v.x) {
-            idx[b + 1] = idx[b];
-            --b;
-        }
-        idx[b + 1] = v;
-    }
-}
-
 // Sorted positions: one thread per slot finds its atom's rank in the cell by
-// the atom index (up to kRankCell atoms, read by neighbouring threads
-// together; larger cells are in order already); the 4th component carries the
-// atom type's bits (0 when the call has no types).
+// the atom index (cells hold tens of atoms at the R/2 cell edge of a specimen,
+// and the threads of a cell read the same entries together).  That is c reads
+// for every one of a crowded cell's c atoms, spread over the chip: putting such
+// a cell in order by one thread's insertion takes c^2 / 4 moves in a row when
+// the arrivals are mixed, minutes at 1.3e5 atoms.  The 4th component carries
+// the atom type's bits (0 when the call has no types).
 __global__ __launch_bounds__(256) void k_sorted_pos(const float *__restrict__ pos, const int32_t *__restrict__ types,
                                                     const int2 *__restrict__ idx,
                                                     const int32_t *__restrict__ cell_start, uint32_t ncells,
@@ -139,12 +119,9 @@ __global__ __launch_bounds__(256) void k_sorted_pos(const float *__restrict__ po
     const int64_t a = v.x;
     const float4 p = make_float4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], __int_as_float(types ? types[a] : 0));
     const int s0 = cell_start[v.y], s1 = cell_start[v.y + 1];
-    int rank = (int)i - s0;
-    if (s1 - s0 <= kRankCell) {
-        rank = 0;
-#pragma unroll 4
-        for (int j = s0; j < s1; ++j) rank += idx[j].x < v.x ? 1 : 0;
-    }
+    int rank = 0;
+#pragma unroll 8
+    for (int j = s0; j < s1; ++j) rank += idx[j].x < v.x ? 1 : 0;
     out[s0 + rank] = p;
 }
 
@@ -426,9 +403,6 @@ static ar_status gather_sort(ar_context *ctx, const float *positions, const int3
     if (n > 0) {
         k_cell_scatter<<<blocks, 256, 0, stream>>>(ctx->g_keys.as<uint32_t>(), ctx->g_slot.as<int32_t>(), n, ncells,
                                                    cell_start, ctx->g_vals.as<int2>());
-        AR_HIP(hipGetLastError());
-        k_cell_order<<<(unsigned)(((int64_t)ncells + 255) / 256), 256, 0, stream>>>(cell_start, ncells,
-                                                                                     ctx->g_vals.as<int2>());
         AR_HIP(hipGetLastError());
         k_sorted_pos<<<blocks, 256, 0, stream>>>(positions, types, ctx->g_vals.as<int2>(), cell_start, ncells,
                                                  ctx->g_sorted.as<float4>());

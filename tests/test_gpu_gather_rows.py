@@ -77,6 +77,12 @@ def test_full_cells_and_long_grids():
     check(wire.astype(f32), centres.astype(f32), 7.0)
 
 
+def test_cells_of_a_hundred_thousand_atoms_keep_the_input_order():
+    gen = np.random.default_rng(4)
+    pos = np.concatenate([gen.normal(0.3, 0.001, (100000, 3)), gen.normal(0.8, 0.02, (20000, 3))]).astype(f32)
+    check(pos[gen.permutation(len(pos))], gen.uniform(0.2, 0.4, (3, 3)).astype(f32), 0.9)
+
+
 def test_more_rois_than_row_counts_are_kept_for():
     gen = np.random.default_rng(4)
     pos = gen.uniform(-3, 3, (5000, 3)).astype(f32)
