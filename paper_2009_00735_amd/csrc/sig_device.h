@@ -334,9 +334,16 @@ __device__ __forceinline__ int eq1_bin(float vx, float vy, float vz, float dx, f
 //   S[n2][k] = sum_n1 h[N2 n1 + n2] e^(-2 pi i k m / 64).
 // m and 64 - m (n1 and 63 - n1) have the same cosine and opposite sines, so
 // the sums run over 32 pairs, cosines of h + h' and sines of h - h'.  The
-// inner sums of D = 32 / N2 directions are one 32-row product with the 32 x
+// inner sums of H = 32 / N2 directions are one 32-row product with the 32 x
 // 32 tables of cosines and sines (v_mfma_f32_32x32x16_f16; row d N2 + n2,
 // column k - kmin), the outer sum of N2 terms is FP32 on the vector unit.
+//
+// A histogram word holds two directions, d in its low 16 bits and d + H in
+// its high 16, counted by adding 1 or 65536: a wavefront passes D = 2 H
+// directions through H histograms, so that clearing and reading them, and
+// reading the atoms, cost half as much per direction.  The low halves are one
+// row tile of the product, the high halves another.  ROIs past kSpan atoms go
+// through the histograms in spans, their spectra added.
 //
 // Exactness: a count c < 2048 is the FP16 number of bit pattern c, c 2^-24, so
 // a pair of histogram words becomes a pair of A operands by packing, an
@@ -346,8 +353,8 @@ __device__ __forceinline__ int eq1_bin(float vx, float vy, float vz, float dx, f
 // were 2^-14, which cost the accumulator up to 10 of its bits, 3e-5 of |X_k|
 // for one atom.)  The table entries are split into two FP16 parts (22 bits);
 // products are exact and accumulate in FP32; 2^14 goes into the outer factors.
-// ROIs of at least 2048 atoms take their counts 10 bits at a time (up to
-// 2^29).
+// Where a pair holds more than 2047 counts, they go in as their low 10 and
+// high 6 bits.
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -355,13 +362,16 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int NB> struct BinPlan {
     static constexpr int N2 = NB / 64;          // rows per direction
-    static constexpr int D = 32 / N2;           // directions per wavefront pass
+    static constexpr int H = 32 / N2;           // histograms per wavefront, two directions each
+    static constexpr int D = 2 * H;             // directions per wavefront pass
+    static constexpr int X = (H + 1) / 2;       // spectra per lane and row tile
     static constexpr int STRIDE = NB + N2;      // words from one histogram to the next: the rows read
                                                 // together (d, n2) then lie in 32 different banks
-    static constexpr int WORDS = D * STRIDE;    // histograms of one wavefront
+    static constexpr int WORDS = H * STRIDE;    // histograms of one wavefront
     static constexpr int TW = N2 == 4 ? 4 : N2 / 2;   // outer factors per lane
-    static_assert(NB >= 256 && NB <= 2048, "8, 4, 2 or 1 directions per pass");
+    static_assert(NB >= 256 && NB <= 2048, "16, 8, 4 or 2 directions per pass");
 };
+constexpr int kSpan = 61440;   // most atoms in the histograms at once (a multiple of every stage, below 65536)
 
 // Per-lane tables, loaded once per kernel; k = the lane's bin (lane % 32).
 template <int NB> struct BinTables {
@@ -398,106 +408,133 @@ template <int NB> struct BinTables {
 };
 
 // A operands of 8 pairs (c[e], p[e]) of at most 2047 counts together, in
-// units of 2^-14: their sums and differences.
-__device__ __forceinline__ void pair_operands(const uint32_t (&c)[8], const uint32_t (&p)[8], f16x8 &sum, f16x8 &diff)
+// units of 2^-14: their sums and differences.  x, y: the counts packed in
+// pairs.
+__device__ __forceinline__ void pair_operands(const uint32_t (&x)[4], const uint32_t (&y)[4], f16x8 &sum, f16x8 &diff)
 {
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        const uint32_t x = c[e] | (c[e + 1] << 16), y = p[e] | (p[e + 1] << 16);
-        const f16x2 s = __builtin_bit_cast(f16x2, x + y) * (_Float16)1024.0f;
-        const f16x2 d = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, x), f16x2{(_Float16)2048.0f, (_Float16)2048.0f}, -s);
-        sum[e] = s.x;
-        sum[e + 1] = s.y;
-        diff[e] = d.x;
-        diff[e + 1] = d.y;
+    for (int e = 0; e < 4; ++e) {
+        const f16x2 s = __builtin_bit_cast(f16x2, x[e] + y[e]) * (_Float16)1024.0f;
+        const f16x2 d =
+            __builtin_elementwise_fma(__builtin_bit_cast(f16x2, x[e]), f16x2{(_Float16)2048.0f, (_Float16)2048.0f}, -s);
+        sum[2 * e] = s.x;
+        sum[2 * e + 1] = s.y;
+        diff[2 * e] = d.x;
+        diff[2 * e + 1] = d.y;
     }
 }
 
-// |X_k| of the wavefront's D histograms: amp[j] is bin lane % 32 of direction
-// 2 j + lane / 32 (D = 1: of the one direction in both halves).  `hist` is the
-// lane's row of its histogram, h its half (lane / 32).
-template <int NB>
-__device__ __forceinline__ void bin_amplitudes(const int *hist, int h, const BinTables<NB> &t, bool large,
-                                               float (&amp)[(BinPlan<NB>::D + 1) / 2])
+// Low (TILE 0) or high (TILE 1) halves of two words, packed.
+template <int TILE> __device__ __forceinline__ uint32_t pack_half(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_perm(b, a, TILE == 0 ? 0x05040100u : 0x07060302u);
+}
+
+// Sums over the rows held by this lane for the directions of one row tile
+// (the low or the high halves of the histogram words).  H = 1: y[0] is the
+// tile's one direction; else y[2 j], y[2 j + 1] are directions 2 j and 2 j + 1
+// (N2 = 4: y[j] alone, direction 2 j + lane / 32).  WIDE: some pair holds more
+// than 2047 counts, so the counts go in as their low 10 and high 6 bits.
+template <int NB, int TILE, bool WIDE>
+__device__ __forceinline__ void tile_rows(const int *up, const int *down, const BinTables<NB> &t,
+                                          float2 (&y)[BinPlan<NB>::H])
 {
     using P = BinPlan<NB>;
     f32x16 C, S;
 #pragma unroll
     for (int i = 0; i < 16; ++i) C[i] = S[i] = 0.f;
-    auto product = [&](int s, f16x8 sum, f16x8 diff) {
-        C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sum, t.c_lo[s], C, 0, 0, 0);
-        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(diff, t.s_lo[s], S, 0, 0, 0);
-        C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sum, t.c_hi[s], C, 0, 0, 0);
-        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(diff, t.s_hi[s], S, 0, 0, 0);
-    };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        uint32_t a[4], b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = pack_half<TILE>((uint32_t)up[(16 * s + 2 * e) * P::N2], (uint32_t)up[(16 * s + 2 * e + 1) * P::N2]);
+            b[e] = pack_half<TILE>((uint32_t)down[-(16 * s + 2 * e) * P::N2],
+                                   (uint32_t)down[-(16 * s + 2 * e + 1) * P::N2]);
+        }
+#pragma unroll
+        for (int hi = 0; hi < (WIDE ? 2 : 1); ++hi) {
+            f16x8 sum, diff;
+            if constexpr (WIDE) {
+                const uint32_t mask = hi ? 0x003f003fu : 0x03ff03ffu;
+                uint32_t c[4], d[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    c[e] = (a[e] >> (hi ? 10 : 0)) & mask;
+                    d[e] = (b[e] >> (hi ? 10 : 0)) & mask;
+                }
+                pair_operands(c, d, sum, diff);
+                sum = sum * (_Float16)(hi ? 1024.0f : 1.0f);
+                diff = diff * (_Float16)(hi ? 1024.0f : 1.0f);
+            } else {
+                pair_operands(a, b, sum, diff);
+            }
+            C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sum, t.c_lo[s], C, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x16_f16(diff, t.s_lo[s], S, 0, 0, 0);
+            C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sum, t.c_hi[s], C, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x16_f16(diff, t.s_hi[s], S, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < 16 / P::TW && d < P::H; ++d) {
+        const int i0 = d * P::TW;
+        float2 z[4];   // four partial sums, as short as the terms allow
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z[i] = cmul(make_float2(C[i0 + i], S[i0 + i]), t.tw[i]);
+#pragma unroll
+        for (int i = 4; i < P::TW; ++i) z[i & 3] = cmac(z[i & 3], make_float2(C[i0 + i], S[i0 + i]), t.tw[i]);
+        y[d] = cadd(cadd(z[0], z[1]), cadd(z[2], z[3]));
+    }
+}
+
+// Adds the spectra of the wavefront's histograms: x[t][j] is bin lane % 32 of
+// direction t H + 2 j + lane / 32 (H = 1: x[0][0] of direction lane / 32).
+// `hist` is the lane's row of its histogram, h its half (lane / 32).  large:
+// pairs past 2047 counts are possible and looked for.
+template <int NB>
+__device__ __forceinline__ void bin_spectra(const int *hist, int h, const BinTables<NB> &t, bool large,
+                                            float2 (&x)[2][BinPlan<NB>::X])
+{
+    using P = BinPlan<NB>;
     const int *up = hist + 8 * h * P::N2, *down = hist + (63 - 8 * h) * P::N2;   // n1 and 63 - n1
-    // pairs past 2047 counts (possible only in ROIs of that many atoms)
     uint32_t any = 0;
     if (large) {
-#pragma unroll 4
-        for (int i = 0; i < 24; ++i)
-            if (!(i & 8)) any |= ((uint32_t)up[i * P::N2] + (uint32_t)down[-i * P::N2]) >> 11;
-    }
-    if (!__any(any != 0)) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            uint32_t c[8], p[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                c[e] = (uint32_t)up[(16 * s + e) * P::N2];
-                p[e] = (uint32_t)down[-(16 * s + e) * P::N2];
-            }
-            f16x8 sum, diff;
-            pair_operands(c, p, sum, diff);
-            product(s, sum, diff);
-        }
-    } else {
 #pragma unroll
         for (int s = 0; s < 2; ++s)
-#pragma unroll 1
-            for (int sh = 0; sh < 30; sh += 10) {
-                uint32_t c[8], p[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    c[e] = ((uint32_t)up[(16 * s + e) * P::N2] >> sh) & 1023u;
-                    p[e] = ((uint32_t)down[-(16 * s + e) * P::N2] >> sh) & 1023u;
-                }
-                f16x8 sum, diff;
-                pair_operands(c, p, sum, diff);
-                // 2^sh in two factors: 2^20 is no FP16 number
-                const _Float16 f = (_Float16)(sh > 0 ? 1024.0f : 1.0f), g = (_Float16)(sh > 10 ? 1024.0f : 1.0f);
-                product(s, sum * f * g, diff * f * g);
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t c = (uint32_t)up[(16 * s + e) * P::N2], p = (uint32_t)down[-(16 * s + e) * P::N2];
+                any |= ((c & 0xffffu) + (p & 0xffffu)) | ((c >> 16) + (p >> 16));
             }
     }
-    // sum of the direction's rows in this lane, values i0 .. i0 + TW - 1
-    auto rows = [&](int i0) {
-        float2 x[4];   // four partial sums, as short as the terms allow
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = cmul(make_float2(C[i0 + i], S[i0 + i]), t.tw[i]);
-#pragma unroll
-        for (int i = 4; i < P::TW; ++i) x[i & 3] = cmac(x[i & 3], make_float2(C[i0 + i], S[i0 + i]), t.tw[i]);
-        return cadd(cadd(x[0], x[1]), cadd(x[2], x[3]));
+    float2 lo[P::H], hi[P::H];
+    // both halves hold half the rows of two directions a and b: swap so that
+    // the lower half sums a and the upper b
+    auto join = [](float2 a, float2 b) {
+        const auto re = __builtin_amdgcn_permlane32_swap(__float_as_uint(a.x), __float_as_uint(b.x), false, false);
+        const auto im = __builtin_amdgcn_permlane32_swap(__float_as_uint(a.y), __float_as_uint(b.y), false, false);
+        return make_float2(__uint_as_float(re[0]) + __uint_as_float(re[1]),
+                           __uint_as_float(im[0]) + __uint_as_float(im[1]));
     };
+    auto add = [&](int tile, const float2 (&y)[P::H]) {
 #pragma unroll
-    for (int j = 0; j < (P::D + 1) / 2; ++j) {
-        float2 x;
-        if constexpr (P::N2 == 4) {
-            x = rows(4 * j);   // rows 8 j + 4 (lane / 32) .. + 3: one direction per half
-        } else if constexpr (P::D == 1) {
-            x = rows(0);
-            x.x += __shfl_xor(x.x, 32);
-            x.y += __shfl_xor(x.y, 32);
-        } else {
-            // both halves hold half the rows of directions 2 j and 2 j + 1:
-            // swap so that each half sums one direction
-            const float2 a = rows(2 * j * P::TW), b = rows((2 * j + 1) * P::TW);
-            const auto re = __builtin_amdgcn_permlane32_swap(__float_as_uint(a.x), __float_as_uint(b.x), false, false);
-            const auto im = __builtin_amdgcn_permlane32_swap(__float_as_uint(a.y), __float_as_uint(b.y), false, false);
-            x = make_float2(__uint_as_float(re[0]) + __uint_as_float(re[1]),
-                            __uint_as_float(im[0]) + __uint_as_float(im[1]));
+        for (int j = 0; j < P::X; ++j) {
+            if constexpr (P::N2 == 4) x[tile][j] = cadd(x[tile][j], y[j]);
+            else if constexpr (P::H > 1) x[tile][j] = cadd(x[tile][j], join(y[2 * j], y[2 * j + 1]));
         }
-        amp[j] = sqrtf(fmaf(x.x, x.x, x.y * x.y));
+    };
+    if (!__any(any > 2047u)) {
+        tile_rows<NB, 0, false>(up, down, t, lo);
+        add(0, lo);
+        tile_rows<NB, 1, false>(up, down, t, hi);
+        add(1, hi);
+    } else {
+        tile_rows<NB, 0, true>(up, down, t, lo);
+        add(0, lo);
+        tile_rows<NB, 1, true>(up, down, t, hi);
+        add(1, hi);
     }
+    if constexpr (P::H == 1) x[0][0] = cadd(x[0][0], join(lo[0], hi[0]));
 }
 
 }  // namespace sig

@@ -16,7 +16,7 @@
 // needed for a ROI whose atoms fit the stage.
 //
 // Windows within 32 bins (every signature in use) take the window products on
-// the matrix cores instead of the FFT (bin_amplitudes); the FFT form above
+// the matrix cores instead of the FFT (bin_spectra); the FFT form above
 // serves wider windows, 4096 bins and the whole spectra of araullo_sdm.
 //
 // Two launch forms share that per-direction code:
@@ -344,24 +344,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, 8))) 
 }
 
 // ------------------------------------- the same launch forms, matrix cores
-// Windows within 32 bins and up to 2048 bins (bin_amplitudes): a wavefront
-// bins D = 2048 / NB directions at a time, so an atom is read from the stage
-// once per D directions, and no FFT passes go through LDS.
+// Windows within 32 bins and up to 2048 bins (bin_spectra): a wavefront bins D
+// = 4096 / NB directions at a time, so an atom is read from the stage once per
+// D directions, and no FFT passes go through LDS.
 //
 // Bound: the FFT form kept the LDS busy 81 % of the time at 1024 bins (471
 // cycles per ROI-direction, 115 of them conflicts of the atomics).  Here the
-// histograms are written and read once: about 280 cycles, the atomics most of
-// it; 249 measured, the LDS busy 77 % of the time, with the vector unit (246
-// instructions per ROI-direction, 393 before) close behind.  200 ROIs of 1006
-// atoms and 10242 directions: 1.21 ms, FFT form 2.04; 500 clipped ROIs in the
-// persistent form 3.14 ms, 5.34.  Three workgroups per CU (12-byte atoms in
-// the stage, 168 registers): two cost 9 %, four (spilling) 10 %.  Reading the
-// next atoms ahead of the atomics changed nothing.
-template <int NB> constexpr size_t wave_bytes_mm() { return ((size_t)BinPlan<NB>::WORDS + kWave) * 4; }
+// histograms are written and read once, and two directions share their words:
+// 179 cycles, the atomics and their conflicts most of it, with the vector unit
+// (235 instructions per ROI-direction, FFT form 393) busy 77 % of the time and
+// now the bound; one direction per word took 249.  200 ROIs of 1006 atoms and
+// 10242 directions: 1.00 ms, one direction per word 1.21, FFT form 2.04; 500
+// clipped ROIs in the persistent form 2.6 ms, 3.14, 5.34.  Three workgroups
+// per CU (12-byte atoms in the stage, 168 registers): two cost 9 %, four
+// (spilling) 10 %.  Reading the next atoms ahead of the atomics changed
+// nothing.
+template <int NB> constexpr size_t wave_bytes_mm() { return (size_t)BinPlan<NB>::WORDS * 4; }
 size_t lds_mm(int nbins, int cap)
 {
     const int n2 = nbins / 64, words = 32 / n2 * (nbins + n2);
-    return (size_t)cap * sizeof(Atom3) + (size_t)kWaves * ((size_t)words + kWave) * 4 + 16;
+    return (size_t)cap * sizeof(Atom3) + (size_t)kWaves * words * 4 + 16;
 }
 
 // Directions of one pass: unit vectors, wave-uniform.
@@ -387,7 +389,7 @@ __device__ __forceinline__ void bin_staged_mm(const Atom3 *xs, int n, const Dirs
 {
     using P = BinPlan<NB>;
     constexpr float last = (float)(NB - 1);
-    constexpr int SLOTS = P::D >= 4 ? 2 : 4;
+    constexpr int SLOTS = P::D >= 8 ? 1 : 8 / P::D;
     const Atom3 *p = xs + lane;
     int g = 0;
     for (; (g + SLOTS) * kWave <= n; g += SLOTS, p += SLOTS * kWave) {
@@ -402,15 +404,16 @@ __device__ __forceinline__ void bin_staged_mm(const Atom3 *xs, int n, const Dirs
 #pragma unroll
         for (int i = 0; i < SLOTS; ++i)
 #pragma unroll
-            for (int d = 0; d < P::D; ++d) atomicAdd(&hist[d * P::STRIDE + b[i][d]], 1);
+            for (int d = 0; d < P::D; ++d) atomicAdd(&hist[d % P::H * P::STRIDE + b[i][d]], d < P::H ? 1 : 65536);
     }
     for (; g * kWave < n; ++g, p += kWave)
         if (g * kWave + lane < n) {
             const Atom3 a = *p;
 #pragma unroll
             for (int d = 0; d < P::D; ++d)
-                atomicAdd(&hist[d * P::STRIDE + eq1_bin(v.x[d], v.y[d], v.z[d], a.x, a.y, a.z, bc.shift, bc.scale, last)],
-                          1);
+                atomicAdd(&hist[d % P::H * P::STRIDE +
+                                eq1_bin(v.x[d], v.y[d], v.z[d], a.x, a.y, a.z, bc.shift, bc.scale, last)],
+                          d < P::H ? 1 : 65536);
         }
 }
 
@@ -423,30 +426,52 @@ template <int NB> __device__ __forceinline__ void zero_hist_mm(int *hist, int la
     wave_lds_sync();
 }
 
-// Window maxima of the finished histograms of directions v .. v + D - 1 (those
-// below v1) of ROI r.
+// Adds the finished histograms' spectra to x.
 template <int NB>
-__device__ __forceinline__ void finish_pass(const int *hist, float *scratch, const BinTables<NB> &t, const WindowSet &ws,
-                                            int lane, bool large, int64_t r, int v, int v1, int n_dir,
-                                            float *__restrict__ images)
+__device__ __forceinline__ void add_spectra(const int *hist, const BinTables<NB> &t, int lane, bool large,
+                                            float2 (&x)[2][BinPlan<NB>::X])
 {
     using P = BinPlan<NB>;
     wave_lds_sync();
-    float amp[(P::D + 1) / 2];
-    const int row = lane & 31, h = lane >> 5;
-    bin_amplitudes<NB>(hist + (row / P::N2) * P::STRIDE + row % P::N2, h, t, large, amp);
+    const int row = lane & 31;
+    bin_spectra<NB>(hist + (row / P::N2) * P::STRIDE + row % P::N2, lane >> 5, t, large, x);
+    wave_lds_sync();
+}
+
+template <int NB> __device__ __forceinline__ void clear_spectra(float2 (&x)[2][BinPlan<NB>::X])
+{
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < BinPlan<NB>::X; ++j) x[t][j] = make_float2(0.f, 0.f);
+}
+
+// Window maxima of the spectra of directions v .. v + D - 1 (those below v1)
+// of ROI r; the amplitudes pass through the histograms' LDS (their words are
+// done with).
+template <int NB>
+__device__ __forceinline__ void finish_pass(const float2 (&x)[2][BinPlan<NB>::X], float *scratch, const BinTables<NB> &t,
+                                            const WindowSet &ws, int lane, int64_t r, int v, int v1, int n_dir,
+                                            float *__restrict__ images)
+{
+    using P = BinPlan<NB>;
+    constexpr int TILES = P::H == 1 ? 1 : 2;
+    static_assert(TILES * P::X * kWave <= P::WORDS, "the amplitudes fit the histograms");
     float *out = images + ((size_t)r * ws.n + (lane >> 4)) * n_dir;
 #pragma unroll
-    for (int j = 0; j < (P::D + 1) / 2; ++j) {
-        wave_lds_sync();
-        scratch[lane] = amp[j];
-        wave_lds_sync();
-        // row lane / 16: window lane / 16 of direction 2 j, then of 2 j + 1
-        const float m0 = row_max16(scratch[t.rd]);
-        const float m1 = P::D == 1 ? 0.f : row_max16(scratch[32 + t.rd]);
-        const int d = v + 2 * j + (lane & 1);
-        if ((lane & 15) < (P::D == 1 ? 1 : 2) && (lane >> 4) < ws.n && d < v1) out[d] = (lane & 1) ? m1 : m0;
+    for (int i = 0; i < TILES * P::X; ++i) {
+        const float2 y = x[i / P::X][i % P::X];
+        scratch[i * kWave + lane] = sqrtf(fmaf(y.x, y.x, y.y * y.y));
     }
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < TILES * P::X; ++i) {
+        // row lane / 16: window lane / 16 of the direction in the lower half, then in the upper
+        const float m0 = row_max16(scratch[i * kWave + t.rd]), m1 = row_max16(scratch[i * kWave + 32 + t.rd]);
+        const int d = v + i / P::X * P::H + 2 * (i % P::X) + (lane & 1);
+        if ((lane & 15) < 2 && (lane >> 4) < ws.n && d < v1) out[d] = (lane & 1) ? m1 : m0;
+    }
+    wave_lds_sync();
 }
 
 // Directions [v0, v1) of ROI r by the wavefronts of the workgroup, as
@@ -459,15 +484,18 @@ __device__ __forceinline__ void process_item_mm(const float4 *__restrict__ rel, 
 {
     constexpr int NB = 1 << LOGNB;
     constexpr int D = BinPlan<NB>::D;
-    float *scratch = reinterpret_cast<float *>(hist + BinPlan<NB>::WORDS);
+    float *scratch = reinterpret_cast<float *>(hist);
     const bool large = nw > 2047;
-    if (nw <= cap) {
+    float2 x[2][BinPlan<NB>::X];
+    if (nw <= cap) {   // the stage is smaller than a span
         for (int v = v0 + wave * D; v < v1; v += kWaves * D) {
             Dirs<D> u;
             u.load(dirs, v, v1);
             zero_hist_mm<NB>(hist, lane);
             bin_staged_mm<NB>(xs, nw, u, bc, hist, lane);
-            finish_pass<NB>(hist, scratch, t, ws, lane, large, r, v, v1, n_dir, images);
+            clear_spectra<NB>(x);
+            add_spectra<NB>(hist, t, lane, large, x);
+            finish_pass<NB>(x, scratch, t, ws, lane, r, v, v1, n_dir, images);
         }
         return;
     }
@@ -478,15 +506,27 @@ __device__ __forceinline__ void process_item_mm(const float4 *__restrict__ rel, 
         if (active) {
             u.load(dirs, v, v1);
             zero_hist_mm<NB>(hist, lane);
+            clear_spectra<NB>(x);
         }
+        int held = 0;   // atoms in the histograms
         for (int c0 = 0; c0 < nw; c0 += cap) {
             const int n = min(cap, nw - c0);
             __syncthreads();
             stage_atoms(xs, rel, off0 + c0, n);
             __syncthreads();
-            if (active) bin_staged_mm<NB>(xs, n, u, bc, hist, lane);
+            if (!active) continue;
+            if (held + n > kSpan) {
+                add_spectra<NB>(hist, t, lane, large, x);
+                zero_hist_mm<NB>(hist, lane);
+                held = 0;
+            }
+            bin_staged_mm<NB>(xs, n, u, bc, hist, lane);
+            held += n;
         }
-        if (active) finish_pass<NB>(hist, scratch, t, ws, lane, large, r, v, v1, n_dir, images);
+        if (active) {
+            add_spectra<NB>(hist, t, lane, large, x);
+            finish_pass<NB>(x, scratch, t, ws, lane, r, v, v1, n_dir, images);
+        }
     }
 }
 
@@ -661,7 +701,7 @@ ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets
     // ROI of 642 directions and 256 bins: 21 workgroups instead of 3, 7 us
     // instead of 83.
     int dirs_per_block = debug ? 64 : 256;
-    const int least = mm ? sig::kWaves * (2048 / nbins) : 4 * sig::kWaves;
+    const int least = mm ? sig::kWaves * (4096 / nbins) : 4 * sig::kWaves;
     while (dirs_per_block > least &&
            n_roi * (int64_t)((n_dir + dirs_per_block - 1) / dirs_per_block) < 8 * 3 * (int64_t)ctx->cu_count)
         dirs_per_block /= 2;

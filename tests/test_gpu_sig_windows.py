@@ -49,3 +49,23 @@ def test_windows_match_the_oracle(orc, nbins, n_dir, windows):
     for cap in (256, 4096):
         plan.set_config(min(3, n_dir), cap, 2)
         assert torch.equal(plan.run(rel, off, R, dev(dirs), w), img)
+
+
+@pytest.mark.parametrize("nbins", [256, 1024, 2048])
+def test_more_atoms_than_the_histograms_hold_at_once(orc, nbins):
+    """ROIs past 65535 atoms go through the 16-bit halves in spans."""
+    from paper_2009_00735_amd import native as nat
+    gen = np.random.default_rng(nbins)
+    ball = gen.normal(size=(70000, 3))
+    ball *= (0.9 * gen.random(70000) ** (1 / 3) / np.linalg.norm(ball, axis=1))[:, None]
+    point = np.tile([[7.1, 0.2, -0.3]], (130001, 1))
+    pos = np.concatenate([ball, point]).astype(np.float32)
+    centres = np.array([[0.0, 0.0, 0.0], [7.0, 0.0, 0.0]], np.float32)
+    d = gen.normal(size=(5, 3))
+    dirs = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    w = np.array([[16, 19], [18, 21], [26, 31], [30, 36]], np.int32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    img, cnt = nat.araullo_signatures(nat.Context(0), dev(pos), dev(centres), 1.0, dev(dirs), nbins, w)
+    ref, rcnt = orc.signatures(pos, centres, 1.0, dirs, nbins, w)
+    assert cnt.cpu().tolist() == [70000, 130001] == list(rcnt)
+    assert_images(img.cpu().numpy(), ref, rcnt[:, None, None])
