@@ -8,20 +8,23 @@
 //                         reciprocal, BF16 (round to nearest even) copy of the
 //                         normalised row, K padded with zeros.
 //   2. k_corr_topk        BF16-input / FP32-accumulate MFMA correlation
-//                         (v_mfma_f32_32x32x16_bf16), 128x128 workgroup tile,
-//                         K in steps of 64 through double-buffered, padded LDS.
-//                         Each workgroup owns a 128-row panel and a segment of
-//                         library columns; the epilogue turns every tile into
-//                         scores |L|^2 - 2<S,L> (the per-row constant |S|^2 is
-//                         dropped) and keeps, per row, the CAND best
+//                         (v_mfma_f32_32x32x16_bf16), workgroup tiles of 128 x
+//                         128 to 256 x 256, K in steps of 32 through a ring of
+//                         LDS stages.  Each workgroup owns a row panel and a
+//                         segment of library columns; the epilogue turns every
+//                         tile into scores |L|^2 - 2<S,L> (the per-row constant
+//                         |S|^2 is dropped) and keeps, per row, the CAND best
 //                         (score, index) pairs in registers: the ranking
 //                         never materialises the score matrix.
-//   3. k_merge            per row, the CAND best over all segments.
+//      k_corr_wave        the same scores for small calls, one wavefront per
+//                         tile; their scores are written out.
+//   3. k_merge, k_select  per row, the CAND best over all segments or scores.
 //   4. k_rescore          exact FP32 sum of squared differences of the
 //                         normalised FP32 images for the CAND candidates,
 //                         sorted by (Delta, index); the first k are returned.
-//                         One workgroup per ROI and one wave per candidate;
-//                         each normalised ROI window is staged in LDS once.
+//                         One workgroup per ROI, its candidates spread over 16
+//                         wavefronts; each normalised ROI window is staged in
+//                         LDS once.
 #include <math.h>
 #include <string.h>
 
@@ -48,54 +51,69 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x)
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ------------------------------------------------------------ normalise + cast
-// grid (n_rows, n_win); writes inv_max[row][w] and out[row][w*n_dir + v].
-// The workgroup of the last window also zeroes the K padding of its row.
-__global__ __launch_bounds__(256) void k_normalise_cast(const float *__restrict__ img, int n_win, int n_dir,
+// grid (rows with padding, n_win); writes inv_max[row][w] and
+// out[row][w*n_dir + v] of the n rows, zeros in the rows past them.  The
+// workgroup of the last window also zeroes the K padding of its row.
+// Bound: memory.  A window of up to 512 kKeep directions stays in registers
+// between its maximum and its copy; read twice, 2000 x 10242 directions took
+// 160 us, now 85.
+constexpr int kKeep = 20;   // pairs per thread: 10240 directions and the two of a geodesic mesh's poles
+__global__ __launch_bounds__(256) void k_normalise_cast(const float *__restrict__ img, int64_t n, int n_win, int n_dir,
                                                         int64_t Kp, float *__restrict__ inv_max,
                                                         uint16_t *__restrict__ out)
 {
-    __shared__ float red[256];
+    __shared__ float red[4];
     const int64_t row = blockIdx.x;
-    const int w = blockIdx.y;
-    const float *src = img + ((size_t)row * n_win + w) * n_dir;
-    float m = 0.0f;
-    for (int v = threadIdx.x; v < n_dir; v += blockDim.x) m = fmaxf(m, src[v]);
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-        __syncthreads();
-    }
-    const float mx = red[0];
-    const float inv = mx > 0.0f ? 1.0f / mx : 0.0f;
-    if (threadIdx.x == 0) inv_max[(size_t)row * n_win + w] = inv;
+    const int w = blockIdx.y, tid = threadIdx.x;
     uint16_t *dst = out + (size_t)row * Kp + (size_t)w * n_dir;
-    if ((n_dir & 1) == 0 && (reinterpret_cast<uintptr_t>(img) & 7) == 0) {
-        // even n_dir (every geodesic mesh: 10 * 4^k + 2 nodes) and an 8-byte
-        // aligned image array: the window's source floats and destination bf16
-        // start 8- and 4-byte aligned,
-        // so convert pairs with one 8-byte load and one 4-byte store per lane
-        const float2 *s2 = reinterpret_cast<const float2 *>(src);
-        uint32_t *d2 = reinterpret_cast<uint32_t *>(dst);
-        for (int v = threadIdx.x; v < n_dir / 2; v += blockDim.x) {
-            const float2 x = s2[v];
-            d2[v] = (uint32_t)f32_to_bf16_rne(x.x * inv) | ((uint32_t)f32_to_bf16_rne(x.y * inv) << 16);
-        }
-    } else {
-        for (int v = threadIdx.x; v < n_dir; v += blockDim.x) dst[v] = f32_to_bf16_rne(src[v] * inv);
-    }
     if (w == n_win - 1) {
         const int64_t K = (int64_t)n_win * n_dir;
-        for (int64_t c = K + threadIdx.x; c < Kp; c += blockDim.x) out[(size_t)row * Kp + c] = 0;
+        for (int64_t c = K + tid; c < Kp; c += 256) out[(size_t)row * Kp + c] = 0;
     }
-}
-
-// zero rows [r0, r1) of a [*][Kp] bf16 matrix
-__global__ __launch_bounds__(256) void k_zero_rows(uint16_t *__restrict__ out, int64_t Kp, int64_t r0, int64_t r1)
-{
-    const int64_t n = (r1 - r0) * Kp;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[r0 * Kp + i] = 0;
+    if (row >= n) {
+        for (int v = tid; v < n_dir; v += 256) dst[v] = 0;
+        return;
+    }
+    const float *src = img + ((size_t)row * n_win + w) * n_dir;
+    // even n_dir (every geodesic mesh: 10 * 4^k + 2 nodes) and an 8-byte
+    // aligned image array: the window's source floats and destination bf16
+    // start 8- and 4-byte aligned, so pairs take one 8-byte load and one
+    // 4-byte store per lane
+    const bool pairs = (n_dir & 1) == 0 && (reinterpret_cast<uintptr_t>(img) & 7) == 0;
+    const float2 *s2 = reinterpret_cast<const float2 *>(src);
+    const int half = n_dir / 2;
+    float2 x[kKeep];
+    float m = 0.0f;
+    if (pairs) {
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j)
+            if (j * 256 + tid < half) x[j] = s2[j * 256 + tid];
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j)
+            if (j * 256 + tid < half) m = fmaxf(m, fmaxf(x[j].x, x[j].y));
+        for (int v = kKeep * 256 + tid; v < half; v += 256) m = fmaxf(m, fmaxf(s2[v].x, s2[v].y));
+    } else {
+        for (int v = tid; v < n_dir; v += 256) m = fmaxf(m, src[v]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    if ((tid & 63) == 0) red[tid >> 6] = m;
+    __syncthreads();
+    const float mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const float inv = mx > 0.0f ? 1.0f / mx : 0.0f;
+    if (tid == 0) inv_max[(size_t)row * n_win + w] = inv;
+    if (pairs) {
+        uint32_t *d2 = reinterpret_cast<uint32_t *>(dst);
+        auto put = [&](int v, float2 y) {
+            d2[v] = (uint32_t)f32_to_bf16_rne(y.x * inv) | ((uint32_t)f32_to_bf16_rne(y.y * inv) << 16);
+        };
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j)
+            if (j * 256 + tid < half) put(j * 256 + tid, x[j]);
+        for (int v = kKeep * 256 + tid; v < half; v += 256) put(v, s2[v]);
+    } else {
+        for (int v = tid; v < n_dir; v += 256) dst[v] = f32_to_bf16_rne(src[v] * inv);
+    }
 }
 
 // |row|^2 of the BF16 copy, FP32; rows >= n_valid get +inf
@@ -413,6 +431,166 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_corr_topk(const uint16_t *__
 // Epilogue lists per row and segment of a tile configuration.
 constexpr int lists_per_row(int cand, int threads, int bm) { return cand == 64 ? 1 : threads / bm; }
 
+// ------------------------------------------------- small calls: wave tiles
+// The same scores where the tiles above would leave most of the chip idle: one
+// wavefront per (32 TM) x (32 TN) tile with a ring of STAGES stages of its own
+// in LDS (64 of K each: 8 KB per 32 x 32) and no barrier; the scores are
+// written out for k_select.  K is summed in the same order by the same
+// instruction, so the scores are those of k_corr_topk.
+// A fill instruction takes 8 rows of 128 bytes, chunk c of row r to chunk
+// c ^ (r & 7) of its LDS row, which keeps the fragment reads free of conflicts.
+template <int N> __device__ __forceinline__ void wait_fills_and_reads()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+template <int T, int STAGES>
+__global__ __launch_bounds__(64) void k_corr_wave(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+                                                  const float *__restrict__ norm2, int64_t Kp, int m_blocks,
+                                                  int n_blocks, int64_t n_cols, float *__restrict__ scores)
+{
+    constexpr int NB = 8 * T, STAGE = NB * 1024;   // fills and bytes per stage
+    static_assert((STAGES & (STAGES - 1)) == 0 && STAGES >= 4 && (STAGES - 2) * NB <= 63, "vmcnt holds 6 bits");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x;
+    // tiles of the same library rows on the same XCD (ids are dealt round-robin)
+    const int j = (int)(blockIdx.x >> 3);
+    const int mb = j % m_blocks, nb = j / m_blocks * 8 + (int)(blockIdx.x & 7);
+    if (nb >= n_blocks) return;
+    const int64_t m0 = (int64_t)mb * 32 * T, n0 = (int64_t)nb * 32 * T;
+    const int row_bytes = (int)(Kp * 2);
+    const int voff = (lane >> 3) * row_bytes + 16 * ((lane & 7) ^ (lane >> 3));
+    const __amdgpu_buffer_rsrc_t rA = panel_rsrc(A + m0 * Kp), rB = panel_rsrc(B + n0 * Kp);
+    const int G = (int)(Kp / 64);
+    auto fill = [&](int g) {
+        unsigned char *st = smem + (size_t)(g & (STAGES - 1)) * STAGE;
+        const int k = min(g, G - 1) * 128;   // past the end: the last step again, not used
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const bool in_a = i < 4 * T;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(in_a ? rA : rB, (lds_void *)(st + i * 1024), 16, voff,
+                                                     (in_a ? i : i - 4 * T) * 8 * row_bytes + k, 0, 0);
+        }
+    };
+    const int rd = (lane & 31) * 128, rx = lane & 7;
+    auto read = [&](int g, bf16x8(&fa)[4][T], bf16x8(&fb)[4][T]) {
+        const unsigned char *st = smem + (size_t)(g & (STAGES - 1)) * STAGE + rd;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int off = 16 * ((2 * q + (lane >> 5)) ^ rx);
+#pragma unroll
+            for (int a = 0; a < T; ++a) fa[q][a] = *reinterpret_cast<const bf16x8 *>(st + a * 4096 + off);
+#pragma unroll
+            for (int c = 0; c < T; ++c) fb[q][c] = *reinterpret_cast<const bf16x8 *>(st + (T + c) * 4096 + off);
+        }
+    };
+    f32x16 acc[T][T];
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+        for (int c = 0; c < T; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][c][r] = 0.0f;
+    bf16x8 fa[2][4][T], fb[2][4][T];
+#pragma unroll
+    for (int g = 0; g < STAGES; ++g) fill(g);
+    wait_fills_and_reads<(STAGES - 1) * NB <= 63 ? (STAGES - 1) * NB : 63>();
+    read(0, fa[0], fb[0]);
+    // step g: the fills of step g + 1 have landed and the reads of step g are
+    // done, so its stage is free for step g + STAGES
+    auto step = [&](int g, int u) {
+        wait_fills_and_reads<(STAGES - 2) * NB>();
+        read(g + 1, fa[u ^ 1], fb[u ^ 1]);
+        fill(g + STAGES);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mfma_frags<T, T>(fa[u][q], fb[u][q], acc);
+    };
+    int g = 0;
+    for (; g + 2 <= G; g += 2) {
+        step(g, 0);
+        step(g + 1, 1);
+    }
+    if (g < G)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mfma_frags<T, T>(fa[0][q], fb[0][q], acc);
+    wait_fills_and_reads<0>();   // no fill outlives the workgroup's LDS
+#pragma unroll
+    for (int c = 0; c < T; ++c) {
+        const int64_t col = n0 + 32 * c + (lane & 31);
+        const float nrm = norm2[col];
+#pragma unroll
+        for (int a = 0; a < T; ++a)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t row = m0 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                scores[row * n_cols + col] = fmaf(-2.0f, acc[a][c][r], nrm);
+            }
+    }
+}
+
+// The CAND smallest (score, column) of each row of scores: the
+// wavefronts of a row (one per 256 columns, up to 16, or 8 for 32, whose lists
+// take the registers of more) keep the best of their columns, the first merges
+// them.
+constexpr int select_waves(int cand) { return cand == 32 ? 8 : 16; }
+template <int CAND>
+__global__ __launch_bounds__(64 * select_waves(CAND)) void k_select(const float *__restrict__ scores, int n_cols,
+                                                 int32_t *__restrict__ cand_idx)
+{
+    constexpr int WAVES = select_waves(CAND);
+    const int waves = (int)blockDim.x >> 6;
+    __shared__ float ls[WAVES * CAND];
+    __shared__ int li[WAVES * CAND];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float *s = scores + (size_t)blockIdx.x * n_cols;
+    int32_t *out = cand_idx + (size_t)blockIdx.x * CAND;
+    if constexpr (CAND == 64) {
+        float t = INFINITY;
+        int i = 0x7fffffff;
+        for (int e = wave * 64; e < n_cols; e += (int)blockDim.x) wave_merge64(t, i, s[e + lane], e + lane, lane);
+        ls[threadIdx.x] = t;
+        li[threadIdx.x] = i;
+        __syncthreads();
+        if (wave) return;
+        for (int w = 1; w < waves; ++w) wave_merge64(t, i, ls[w * 64 + lane], li[w * 64 + lane], lane);
+        out[lane] = i;
+    } else {
+        auto keep = [&](int j, float bs, int bi) {
+            if (lane == 0) {
+                ls[wave * CAND + j] = bs;
+                li[wave * CAND + j] = bi;
+            }
+        };
+        if (n_cols <= 4 * (int)blockDim.x) {   // at most four columns per lane
+            TopList<4> t;
+            t.init();
+            float x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = q * (int)blockDim.x + (int)threadIdx.x;
+                x[q] = e < n_cols ? s[e] : NAN;   // no pair is less
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t.insert(x[q], q * (int)blockDim.x + (int)threadIdx.x);
+            wave_select<CAND>(t, keep);
+        } else {
+            TopList<CAND> t;
+            t.init();
+            for (int e = threadIdx.x; e < n_cols; e += (int)blockDim.x) t.insert(s[e], e);
+            wave_select<CAND>(t, keep);
+        }
+        __syncthreads();
+        if (wave) return;
+        static_assert(WAVES * CAND <= 4 * 64, "at most four entries per lane");
+        TopList<4> t;
+        t.init();
+        for (int e = lane; e < waves * CAND; e += 64) t.insert(ls[e], li[e]);
+        wave_select<CAND>(t, [&](int j, float, int bi) {
+            if (lane == 0) out[j] = bi;
+        });
+    }
+}
+
 // ------------------------------------------------------------ merge
 // One wave per row: the CAND smallest (score, index) over n_lists lists.
 template <int CAND>
@@ -453,9 +631,13 @@ __global__ __launch_bounds__(256) void k_merge64(const float *__restrict__ in_s,
 
 // ------------------------------------------------------------ FP32 rescore
 // One workgroup per ROI row: Delta for each candidate from the FP32 images,
-// then the k best by (Delta, index).
-template <int CAND, bool STAGE>
-__global__ __launch_bounds__(256) void k_rescore(const float *__restrict__ S, const float *__restrict__ inv_s,
+// then the k best by (Delta, index).  Bound: the candidates' rows from memory.
+// Sixteen wavefronts, one candidate each of 16: a call of 16 ROIs and 642
+// directions takes 37 us, with four wavefronts 45; 20000 ROIs and 10242
+// directions 148.4 ms, 149.2.
+constexpr int kRescoreWaves = 16;
+template <int CAND, bool STAGE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_rescore(const float *__restrict__ S, const float *__restrict__ inv_s,
                                                  const float *__restrict__ L, const float *__restrict__ inv_l,
                                                  const int32_t *__restrict__ cand_idx, int n_win, int n_dir,
                                                  int64_t n_lib, int k, int32_t *__restrict__ top_idx,
@@ -465,7 +647,8 @@ __global__ __launch_bounds__(256) void k_rescore(const float *__restrict__ S, co
     extern __shared__ float stage[];
     __shared__ float ds[CAND];
     __shared__ int di[CAND];
-    constexpr int PER = CAND / 4;   // candidates per wave
+    constexpr int PER = CAND / WAVES;   // candidates per wave
+    constexpr int THREADS = 64 * WAVES, AHEAD = 64 / WAVES;
     const int64_t r = blockIdx.x;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const float *srow = S + (size_t)r * n_win * n_dir;
@@ -473,7 +656,7 @@ __global__ __launch_bounds__(256) void k_rescore(const float *__restrict__ S, co
     float acc[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int l = cand_idx[(size_t)r * CAND + wave + 4 * q];
+        const int l = cand_idx[(size_t)r * CAND + wave + WAVES * q];
         cl[q] = (l >= 0 && l < n_lib) ? l : -1;
         acc[q] = 0.0f;
     }
@@ -482,14 +665,14 @@ __global__ __launch_bounds__(256) void k_rescore(const float *__restrict__ S, co
         const float *src = srow + (size_t)w * n_dir;
         if (STAGE) {
             __syncthreads();
-            // the ROI's normalised window, sixteen loads in flight per thread
-            for (int v0 = threadIdx.x; v0 < n_dir; v0 += 256 * 16) {
-                float x[16];
+            // the ROI's normalised window, AHEAD loads in flight per thread
+            for (int v0 = threadIdx.x; v0 < n_dir; v0 += THREADS * AHEAD) {
+                float x[AHEAD];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) x[e] = v0 + 256 * e < n_dir ? src[v0 + 256 * e] : 0.0f;
+                for (int e = 0; e < AHEAD; ++e) x[e] = v0 + THREADS * e < n_dir ? src[v0 + THREADS * e] : 0.0f;
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (v0 + 256 * e < n_dir) stage[v0 + 256 * e] = x[e] * is;
+                for (int e = 0; e < AHEAD; ++e)
+                    if (v0 + THREADS * e < n_dir) stage[v0 + THREADS * e] = x[e] * is;
             }
             __syncthreads();
         }
@@ -514,30 +697,12 @@ __global__ __launch_bounds__(256) void k_rescore(const float *__restrict__ S, co
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
         if (lane == 0) {
-            ds[wave + 4 * q] = cl[q] >= 0 ? a : INFINITY;
-            di[wave + 4 * q] = cl[q] >= 0 ? cl[q] : 0x7fffffff;
+            ds[wave + WAVES * q] = cl[q] >= 0 ? a : INFINITY;
+            di[wave + WAVES * q] = cl[q] >= 0 ? cl[q] : 0x7fffffff;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // insertion sort of CAND entries by (Delta, index)
-        for (int a = 1; a < CAND; ++a) {
-            const float vs = ds[a];
-            const int vi = di[a];
-            int b = a - 1;
-            while (b >= 0 && (ds[b] > vs || (ds[b] == vs && di[b] > vi))) {
-                ds[b + 1] = ds[b];
-                di[b + 1] = di[b];
-                --b;
-            }
-            ds[b + 1] = vs;
-            di[b + 1] = vi;
-        }
-        for (int j = 0; j < k; ++j) {
-            top_idx[(size_t)r * k + j] = di[j] == 0x7fffffff ? -1 : di[j];
-            top_score[(size_t)r * k + j] = ds[j];
-        }
-    }
+    if (wave == 0) rank_candidates<CAND>(ds, di, lane, k, top_idx + (size_t)r * k, top_score + (size_t)r * k);
 }
 
 // The ROI window is staged in LDS when n_dir floats fit beside the static
@@ -547,16 +712,17 @@ ar_status launch_rescore(ar_context *ctx, const float *images, const ar_library 
                          int32_t *top_idx, float *top_score, hipStream_t s)
 {
     const size_t stage = sizeof(float) * (size_t)lib->n_dir;
+    constexpr int W = kRescoreWaves;
     if (stage + 4096 <= (size_t)ctx->lds_per_block) {
         if (stage > 65536)   // on every launch: the attribute belongs to the current device
-            AR_HIP(hipFuncSetAttribute((const void *)k_rescore<CAND, true>,
+            AR_HIP(hipFuncSetAttribute((const void *)k_rescore<CAND, true, W>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)stage));
-        k_rescore<CAND, true><<<(unsigned)n_roi, 256, stage, s>>>(images, ctx->i_inv.as<float>(), lib->ref,
+        k_rescore<CAND, true, W><<<(unsigned)n_roi, 64 * W, stage, s>>>(images, ctx->i_inv.as<float>(), lib->ref,
                                                                   lib->inv_max.as<float>(),
                                                                   ctx->i_merge_idx.as<int32_t>(), lib->n_win,
                                                                   lib->n_dir, lib->n_lib, k, top_idx, top_score);
     } else {
-        k_rescore<CAND, false><<<(unsigned)n_roi, 256, 0, s>>>(images, ctx->i_inv.as<float>(), lib->ref,
+        k_rescore<CAND, false, W><<<(unsigned)n_roi, 64 * W, 0, s>>>(images, ctx->i_inv.as<float>(), lib->ref,
                                                                lib->inv_max.as<float>(),
                                                                ctx->i_merge_idx.as<int32_t>(), lib->n_win,
                                                                lib->n_dir, lib->n_lib, k, top_idx, top_score);
@@ -671,20 +837,52 @@ int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 ar_status normalise_cast(const float *img, int64_t n, int64_t n_pad, int n_win, int n_dir, int64_t Kp, float *inv,
                          uint16_t *out, hipStream_t s)
 {
-    dim3 grid((unsigned)n, (unsigned)n_win);
-    k_normalise_cast<<<grid, 256, 0, s>>>(img, n_win, n_dir, Kp, inv, out);
+    k_normalise_cast<<<dim3((unsigned)n_pad, (unsigned)n_win), 256, 0, s>>>(img, n, n_win, n_dir, Kp, inv, out);
     AR_HIP(hipGetLastError());
-    if (n_pad > n) {
-        k_zero_rows<<<256, 256, 0, s>>>(out, Kp, n, n_pad);
-        AR_HIP(hipGetLastError());
-    }
     return AR_OK;
 }
 
 // Correlation (main and optional tail launch), merge, FP32 rescore and the
 // optional copy of the BF16-stage candidates, for CAND candidates per row.
+// Which correlation a call takes by default; fewer than 256 of the 256 x 256
+// tiles leave CUs idle, the smaller forms are less efficient per tile.  Counted
+// in tiles per CU (256 CUs); us per call of 1000 ROIs and 10242 directions
+// unless stated, 256 x 256 / the form taken / the next larger one:
+//   wave tile 32    at most 2 per CU, or up to 32 ROIs (8 per CU, where the
+//                   library's bytes bound either): 64 x 4000 at 2562
+//                   directions 336 / 79 / 104; 32 x 20000 1207 / 451 / 559
+//   wave tile 64    at most 3 per CU: 1000 library rows 1353 / 624 / 854; 4
+//                   per CU (4000 rows) 1118 against 940 for 128 x 128
+//   128 x 128       at most 1 per CU: 4000 rows 1428 / 940 / 1191
+//   128 x 256       at most 1 per CU: 8000 rows 1474 / 1275 / 1311 (256 x 128)
+// All of them give the same scores, and so the same candidates.
+enum class CorrForm { tiles, half, quarter, wave64, wave32 };
+CorrForm corr_form(int64_t n_roi, int64_t n_pad, int64_t cus)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return (n_roi + bm - 1) / bm * (n_pad / bn); };
+    if (tiles(32, 32) <= 2 * cus || (n_roi <= 32 && tiles(32, 32) <= 8 * cus)) return CorrForm::wave32;
+    if (tiles(64, 64) <= 3 * cus) return CorrForm::wave64;
+    if (tiles(128, 128) <= cus) return CorrForm::quarter;
+    return tiles(128, 256) <= cus ? CorrForm::half : CorrForm::tiles;
+}
+
+template <int T, int STAGES>
+ar_status launch_wave(ar_context *ctx, const ar_library *lib, int64_t rows, float *scores, hipStream_t s)
+{
+    const int m_blocks = (int)(rows / (32 * T)), n_blocks = (int)(lib->n_pad / (32 * T));
+    const unsigned blocks = (unsigned)((n_blocks + 7) / 8 * 8 * m_blocks);
+    constexpr size_t lds = (size_t)STAGES * 8192 * T;
+    static_assert(lds <= 65536, "needs no attribute");
+    AR_CHECK((size_t)ctx->lds_per_block >= lds, "correlation tile needs %zu bytes of LDS per workgroup", lds);
+    k_corr_wave<T, STAGES><<<blocks, 64, lds, s>>>(ctx->i_bf16.as<uint16_t>(), lib->bf16.as<uint16_t>(),
+                                                   lib->norm2.as<float>(), lib->Kp, m_blocks, n_blocks, lib->n_pad,
+                                                   scores);
+    AR_HIP(hipGetLastError());
+    return AR_OK;
+}
+
 template <int CAND>
-ar_status run_index(ar_context *ctx, const CorrCfg &cfg, const CorrCfg &tail_cfg, bool split, const CorrLaunch &main_l,
+ar_status run_index(ar_context *ctx, CorrForm form, int64_t rows, const CorrCfg &cfg, const CorrCfg &tail_cfg, bool split, const CorrLaunch &main_l,
                     const CorrLaunch &tail_l, int n_lists, const float *images, const ar_library *lib, int64_t n_roi,
                     int k, int32_t *top_idx, float *top_score, int32_t *cand_idx, hipStream_t s)
 {
@@ -692,9 +890,19 @@ ar_status run_index(ar_context *ctx, const CorrCfg &cfg, const CorrCfg &tail_cfg
     float *cs = ctx->i_cand_score.as<float>();
     int32_t *ci = ctx->i_cand_idx.as<int32_t>();
     int32_t *merged = ctx->i_merge_idx.as<int32_t>();
-    AR_TRY(launch_corr<CAND>(ctx, cfg, A, lib, main_l, cs, ci, s));
-    if (split) AR_TRY(launch_corr<CAND>(ctx, tail_cfg, A, lib, tail_l, cs, ci, s));
-    if constexpr (CAND == 64)
+    const bool waves = form == CorrForm::wave32 || form == CorrForm::wave64;
+    if (form == CorrForm::wave32) {
+        AR_TRY((launch_wave<1, 4>(ctx, lib, rows, cs, s)));
+    } else if (form == CorrForm::wave64) {
+        AR_TRY((launch_wave<2, 4>(ctx, lib, rows, cs, s)));
+    } else {
+        AR_TRY(launch_corr<CAND>(ctx, cfg, A, lib, main_l, cs, ci, s));
+        if (split) AR_TRY(launch_corr<CAND>(ctx, tail_cfg, A, lib, tail_l, cs, ci, s));
+    }
+    if (waves)
+        k_select<CAND><<<(unsigned)n_roi, 64 * (int)std::min<int64_t>(select_waves(CAND), lib->n_pad / 256), 0, s>>>(
+            cs, (int)lib->n_pad, merged);
+    else if constexpr (CAND == 64)
         k_merge64<<<(unsigned)((n_roi + 3) / 4), 256, 0, s>>>(cs, ci, n_lists, n_roi, merged);
     else
         k_merge<CAND><<<(unsigned)((n_roi + 3) / 4), 256, 0, s>>>(cs, ci, n_lists, n_roi, merged);
@@ -822,7 +1030,8 @@ ar_status index_orientations_ex(ar_context *ctx, const float *images, int64_t n_
     AR_CHECK(lib->ctx == ctx, "library belongs to another context");
     AR_HIP(hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    // Default tile: 256 x 256 (8 waves of 4 x 2 MFMA tiles).  Longer
+    // Small calls take the form that fills the chip (corr_form); beyond them
+    // the default tile is 256 x 256 (8 waves of 4 x 2 MFMA tiles).  Longer
     // candidate lists (cand = 32 per thread, 64 per wave) do not fit beside
     // the 8-wave tile's accumulators, so cand >= 32 takes the same 256 x 256
     // tile on 4 waves of 4 x 4 MFMA tiles (one wave per SIMD, 512 registers
@@ -838,9 +1047,13 @@ ar_status index_orientations_ex(ar_context *ctx, const float *images, int64_t n_
     // / 18.7; 5000 x 20000 (7) 10.5 / 9.8; 10000 x 40000 (5) 33.7-33.8 /
     // 34.2; 20000 x 12500 (2) 27.6-27.8 / 28.0.
     const int64_t m_pad = idx::round_up(n_roi, idx::kPadM);
+    const idx::CorrForm form =
+        ctx->corr_tile_set ? idx::CorrForm::tiles : idx::corr_form(n_roi, lib->n_pad, ctx->cu_count);
     idx::CorrCfg cfg = ctx->corr_tile_set ? idx::CorrCfg{ctx->corr_waves, ctx->corr_wtm, ctx->corr_wtn, ctx->corr_bk}
-                       : cand >= 32       ? idx::CorrCfg{4, 4, 4, idx::kBK}
-                                          : idx::CorrCfg{8, 4, 2, idx::kBK};
+                       : form == idx::CorrForm::quarter ? idx::CorrCfg{4, 2, 2, idx::kBK}
+                       : form == idx::CorrForm::half    ? idx::CorrCfg{8, 2, 2, idx::kBK}
+                       : cand >= 32                     ? idx::CorrCfg{4, 4, 4, idx::kBK}
+                                                        : idx::CorrCfg{8, 4, 2, idx::kBK};
     const int m_blocks = (int)(m_pad / cfg.bm());
     const int n_tiles = (int)(lib->n_pad / cfg.bn());
     // segments: a workgroup walks tiles_per_seg column tiles of one row block.
@@ -874,7 +1087,8 @@ ar_status index_orientations_ex(ar_context *ctx, const float *images, int64_t n_
             }
         }
     }
-    if (!ctx->corr_tile_set && cand == 16 && tiles_per_seg >= 6) cfg = idx::CorrCfg{4, 4, 4, idx::kBK};
+    if (!ctx->corr_tile_set && form == idx::CorrForm::tiles && cand == 16 && tiles_per_seg >= 6)
+        cfg = idx::CorrCfg{4, 4, 4, idx::kBK};
     // One-tile segments whose last round is partial (small calls): the whole
     // rounds run the main tile and the remaining columns a tile of the same
     // height and half the width (4 waves), all in one more round.  Every
@@ -906,20 +1120,27 @@ ar_status index_orientations_ex(ar_context *ctx, const float *images, int64_t n_
                         (split ? tail_l.n_seg * idx::lists_per_row(cand, tail_cfg.threads(), tail_cfg.bm()) : 0);
     main_l.list_stride = tail_l.list_stride = n_lists;
 
-    AR_TRY(ctx->i_bf16.reserve(sizeof(uint16_t) * (size_t)m_pad * lib->Kp));
+    const int64_t rows = form == idx::CorrForm::wave32   ? idx::round_up(n_roi, 32)
+                         : form == idx::CorrForm::wave64 ? idx::round_up(n_roi, 64)
+                                                         : m_pad;   // with padding
+    AR_TRY(ctx->i_bf16.reserve(sizeof(uint16_t) * (size_t)rows * lib->Kp));
     AR_TRY(ctx->i_inv.reserve(sizeof(float) * (size_t)n_roi * lib->n_win));
-    AR_TRY(ctx->i_cand_score.reserve(sizeof(float) * (size_t)m_pad * n_lists * cand));
-    AR_TRY(ctx->i_cand_idx.reserve(sizeof(int32_t) * (size_t)m_pad * n_lists * cand));
+    if (form == idx::CorrForm::wave32 || form == idx::CorrForm::wave64) {
+        AR_TRY(ctx->i_cand_score.reserve(sizeof(float) * (size_t)rows * lib->n_pad));
+    } else {
+        AR_TRY(ctx->i_cand_score.reserve(sizeof(float) * (size_t)m_pad * n_lists * cand));
+        AR_TRY(ctx->i_cand_idx.reserve(sizeof(int32_t) * (size_t)m_pad * n_lists * cand));
+    }
     AR_TRY(ctx->i_merge_idx.reserve(sizeof(int32_t) * (size_t)n_roi * cand));
 
-    AR_TRY(idx::normalise_cast(images, n_roi, m_pad, lib->n_win, lib->n_dir, lib->Kp, ctx->i_inv.as<float>(),
+    AR_TRY(idx::normalise_cast(images, n_roi, rows, lib->n_win, lib->n_dir, lib->Kp, ctx->i_inv.as<float>(),
                                ctx->i_bf16.as<uint16_t>(), s));
     switch (cand) {
-    case 16: AR_TRY(idx::run_index<16>(ctx, cfg, tail_cfg, split, main_l, tail_l, n_lists, images, lib, n_roi, k, top_idx,
+    case 16: AR_TRY(idx::run_index<16>(ctx, form, rows, cfg, tail_cfg, split, main_l, tail_l, n_lists, images, lib, n_roi, k, top_idx,
                                        top_score, cand_idx, s)); break;
-    case 32: AR_TRY(idx::run_index<32>(ctx, cfg, tail_cfg, split, main_l, tail_l, n_lists, images, lib, n_roi, k, top_idx,
+    case 32: AR_TRY(idx::run_index<32>(ctx, form, rows, cfg, tail_cfg, split, main_l, tail_l, n_lists, images, lib, n_roi, k, top_idx,
                                        top_score, cand_idx, s)); break;
-    default: AR_TRY(idx::run_index<64>(ctx, cfg, tail_cfg, split, main_l, tail_l, n_lists, images, lib, n_roi, k, top_idx,
+    default: AR_TRY(idx::run_index<64>(ctx, form, rows, cfg, tail_cfg, split, main_l, tail_l, n_lists, images, lib, n_roi, k, top_idx,
                                        top_score, cand_idx, s)); break;
     }
     return AR_OK;
