@@ -446,13 +446,16 @@ __global__ __launch_bounds__(256) void k_sparse_norm(const float *__restrict__ i
 
 // grid (n_grp, n_win), 8 ROIs per group.  q8[grp][w][slab bytes]: byte
 // v * 8 + j = round(255 s) of ROI grp * 8 + j at node v, s the normalised value
-// (clamped to [0, 1]); node n_dir, ROIs past n_roi and padding are zero.  The
-// eight window maxima are taken together (one pass, eight loads in flight).
-__global__ __launch_bounds__(256) void k_sparse_norm8(const float *__restrict__ img, int64_t n_roi, int n_win,
-                                                      int n_dir, int64_t slab, float *__restrict__ inv_s,
-                                                      uint32_t *__restrict__ q8)
+// (clamped to [0, 1]); node n_dir, ROIs past n_roi and padding are zero.
+// Bound: memory.  The first kNormKeep nodes of every thread stay in registers
+// between the eight maxima and the codes (2000 ROIs x 10242 directions
+// 81 us; read twice 207).
+constexpr int kNormThreads = 1024, kNormKeep = 10;
+__global__ __launch_bounds__(kNormThreads) void k_sparse_norm8(const float *__restrict__ img, int64_t n_roi, int n_win,
+                                                               int n_dir, int64_t slab, float *__restrict__ inv_s,
+                                                               uint32_t *__restrict__ q8)
 {
-    __shared__ float part[4][8];
+    __shared__ float part[kNormThreads / 64][8];
     __shared__ float inv[8];
     const int64_t grp = blockIdx.x;
     const int w = blockIdx.y;
@@ -460,57 +463,52 @@ __global__ __launch_bounds__(256) void k_sparse_norm8(const float *__restrict__ 
     const int nr = (int)min((int64_t)8, n_roi - grp * 8);
     const float *src = img + ((size_t)grp * 8 * n_win + w) * n_dir;   // ROI j at src + j * n_win * n_dir
     const size_t rs = (size_t)n_win * n_dir;
-    // a thread takes four nodes (stride 256) of all eight ROIs per step: 32
-    // independent loads in flight
-    float m[8];
+    float x[kNormKeep][8], m[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) m[j] = 0.0f;
-    for (int v0 = tid; v0 < n_dir; v0 += 1024)
+    for (int e = 0; e < kNormKeep; ++e)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int v = v0 + 256 * e;
-                if (j < nr && v < n_dir) m[j] = fmaxf(m[j], src[j * rs + v]);
-            }
+        for (int j = 0; j < 8; ++j) {
+            const int v = tid + kNormThreads * e;
+            x[e][j] = j < nr && v < n_dir ? src[j * rs + v] : 0.0f;
+        }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
+        m[j] = 0.0f;
+#pragma unroll
+        for (int e = 0; e < kNormKeep; ++e) m[j] = fmaxf(m[j], x[e][j]);
+        if (j < nr)
+            for (int v = tid + kNormThreads * kNormKeep; v < n_dir; v += kNormThreads) m[j] = fmaxf(m[j], src[j * rs + v]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) m[j] = fmaxf(m[j], __shfl_xor(m[j], off));
         if (lane == 0) part[wave][j] = m[j];
     }
     __syncthreads();
     if (tid < 8) {
-        const float mx = fmaxf(fmaxf(part[0][tid], part[1][tid]), fmaxf(part[2][tid], part[3][tid]));
+        float mx = part[0][tid];
+#pragma unroll
+        for (int u = 1; u < kNormThreads / 64; ++u) mx = fmaxf(mx, part[u][tid]);
         inv[tid] = mx > 0.0f ? 1.0f / mx : 0.0f;
         if (tid < nr) inv_s[(size_t)(grp * 8 + tid) * n_win + w] = inv[tid];
     }
     __syncthreads();
-    float iv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) iv[j] = inv[j];
-    // node v's two words (ROIs 0-3, 4-7); four nodes per thread and step
     uint2 *dst = reinterpret_cast<uint2 *>(q8 + ((size_t)grp * n_win + w) * (slab >> 2));
     const int n_nodes = (int)(slab >> 3);   // slab / 8 bytes: nodes incl. the zero node and padding
-    for (int v0 = tid; v0 < n_nodes; v0 += 1024) {
-        float x[4][8];
+    // node v's two words (ROIs 0-3, 4-7)
+    auto put = [&](int v, const float (&y)[8]) {
+        uint32_t word[2] = {0u, 0u};
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+        for (int j = 0; j < 8; ++j)
+            word[j >> 2] |= (uint32_t)rintf(255.0f * fminf(fmaxf(y[j] * inv[j], 0.0f), 1.0f)) << (8 * (j & 3));
+        dst[v] = make_uint2(word[0], word[1]);
+    };
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int v = v0 + 256 * e;
-                x[e][j] = (j < nr && v < n_dir) ? src[j * rs + v] : 0.0f;
-            }
+    for (int e = 0; e < kNormKeep; ++e)
+        if (tid + kNormThreads * e < n_nodes) put(tid + kNormThreads * e, x[e]);
+    for (int v = tid + kNormThreads * kNormKeep; v < n_nodes; v += kNormThreads) {
+        float y[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int v = v0 + 256 * e;
-            if (v >= n_nodes) break;
-            uint32_t word[2] = {0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                word[j >> 2] |= (uint32_t)rintf(255.0f * fminf(fmaxf(x[e][j] * iv[j], 0.0f), 1.0f)) << (8 * (j & 3));
-            dst[v] = make_uint2(word[0], word[1]);
-        }
+        for (int j = 0; j < 8; ++j) y[j] = j < nr && v < n_dir ? src[j * rs + v] : 0.0f;
+        put(v, y);
     }
 }
 
@@ -825,8 +823,11 @@ __global__ __launch_bounds__(256) void k_sparse_merge(const float *__restrict__ 
 // (n_dir floats), so the per-entry gathers read LDS; otherwise they read the
 // image in global memory.  Either way d = x * (1 / max) - R_i as in the
 // screens' normalisation, the square accumulated with one FMA.
+// Sixteen wavefronts, one candidate each of 16: 2000 ROIs, 1000 entries 98 us,
+// with four wavefronts 154.
+constexpr int kRescoreWaves = 16;
 template <int CAND, bool STAGE>
-__global__ __launch_bounds__(256) void k_sparse_rescore(
+__global__ __launch_bounds__(64 * kRescoreWaves) void k_sparse_rescore(
     const float *__restrict__ S, const float *__restrict__ inv_s, int n_win, int n_dir,
     const int32_t *__restrict__ cseg, const float *__restrict__ sval_w, const uint16_t *__restrict__ lut_gi,
     int n_hat, const int64_t *__restrict__ phase_start, int n_phase, int64_t n_lib,
@@ -836,7 +837,8 @@ __global__ __launch_bounds__(256) void k_sparse_rescore(
     extern __shared__ float stage[];
     __shared__ float ds[CAND];
     __shared__ int di[CAND];
-    constexpr int PER = CAND / 4;   // candidates per wave
+    constexpr int WAVES = kRescoreWaves, PER = CAND / WAVES;   // candidates per wave
+    constexpr int THREADS = 64 * WAVES, AHEAD = 64 / WAVES;
     const int64_t r = blockIdx.x;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const float *srow = S + (size_t)r * n_win * n_dir;
@@ -845,7 +847,7 @@ __global__ __launch_bounds__(256) void k_sparse_rescore(
     float acc[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int l = cand_idx[(size_t)r * CAND + wave + 4 * q];
+        const int l = cand_idx[(size_t)r * CAND + wave + WAVES * q];
         cl[q] = l;
         cph[q] = (l >= 0 && l < n_lib) ? phase_of(l, phase_start, n_phase) : -1;
         acc[q] = 0.0f;
@@ -855,14 +857,14 @@ __global__ __launch_bounds__(256) void k_sparse_rescore(
         const float *src = srow + (size_t)w * n_dir;
         if (STAGE) {
             __syncthreads();
-            // sixteen loads in flight per thread
-            for (int v0 = threadIdx.x; v0 < n_dir; v0 += 256 * 16) {
-                float x[16];
+            // AHEAD loads in flight per thread
+            for (int v0 = threadIdx.x; v0 < n_dir; v0 += THREADS * AHEAD) {
+                float x[AHEAD];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) x[e] = v0 + 256 * e < n_dir ? src[v0 + 256 * e] : 0.0f;
+                for (int e = 0; e < AHEAD; ++e) x[e] = v0 + THREADS * e < n_dir ? src[v0 + THREADS * e] : 0.0f;
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (v0 + 256 * e < n_dir) stage[v0 + 256 * e] = x[e] * iw;
+                for (int e = 0; e < AHEAD; ++e)
+                    if (v0 + THREADS * e < n_dir) stage[v0 + THREADS * e] = x[e] * iw;
             }
             __syncthreads();
         }
@@ -888,29 +890,12 @@ __global__ __launch_bounds__(256) void k_sparse_rescore(
         for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
         if (lane == 0) {
             const bool ok = cph[q] >= 0;
-            ds[wave + 4 * q] = ok ? a : INFINITY;
-            di[wave + 4 * q] = ok ? cl[q] : 0x7fffffff;
+            ds[wave + WAVES * q] = ok ? a : INFINITY;
+            di[wave + WAVES * q] = ok ? cl[q] : 0x7fffffff;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int a = 1; a < CAND; ++a) {
-            const float vs = ds[a];
-            const int vi = di[a];
-            int b = a - 1;
-            while (b >= 0 && pair_less(vs, vi, ds[b], di[b])) {
-                ds[b + 1] = ds[b];
-                di[b + 1] = di[b];
-                --b;
-            }
-            ds[b + 1] = vs;
-            di[b + 1] = vi;
-        }
-        for (int j = 0; j < k; ++j) {
-            top_idx[(size_t)r * k + j] = di[j] == 0x7fffffff ? -1 : di[j];
-            top_score[(size_t)r * k + j] = ds[j];
-        }
-    }
+    if (wave == 0) rank_candidates<CAND>(ds, di, lane, k, top_idx + (size_t)r * k, top_score + (size_t)r * k);
 }
 
 // Slab bytes of one (ROI group, window): n_dir + 1 nodes (the last is the
@@ -950,12 +935,12 @@ ar_status merge_rescore(ar_context *ctx, const ar_sparse_lut *lut, const float *
     const size_t stage = sizeof(float) * (size_t)lut->n_dir;
     if (stage + 4096 <= (size_t)ctx->lds_per_block) {
         AR_TRY(allow_lds(k_sparse_rescore<CAND, true>, stage));
-        k_sparse_rescore<CAND, true><<<(unsigned)n_roi, 256, stage, s>>>(
+        k_sparse_rescore<CAND, true><<<(unsigned)n_roi, 64 * kRescoreWaves, stage, s>>>(
             images, ctx->sp_inv.as<float>(), lut->n_win, lut->n_dir, lut->cseg.as<int32_t>(),
             lut->sval_w.as<float>(), lut->lut_gi.as<uint16_t>(), lut->n_hat, lut->phase_start.as<int64_t>(),
             lut->n_phase, lut->n_lib, ctx->sp_merge.as<int32_t>(), k, top_idx, top_score);
     } else {
-        k_sparse_rescore<CAND, false><<<(unsigned)n_roi, 256, 0, s>>>(
+        k_sparse_rescore<CAND, false><<<(unsigned)n_roi, 64 * kRescoreWaves, 0, s>>>(
             images, ctx->sp_inv.as<float>(), lut->n_win, lut->n_dir, lut->cseg.as<int32_t>(),
             lut->sval_w.as<float>(), lut->lut_gi.as<uint16_t>(), lut->n_hat, lut->phase_start.as<int64_t>(),
             lut->n_phase, lut->n_lib, ctx->sp_merge.as<int32_t>(), k, top_idx, top_score);
@@ -1018,7 +1003,7 @@ ar_status run_screen8(ar_context *ctx, const ar_sparse_lut *lut, const float *im
     AR_CHECK((size_t)ctx->lds_per_block >= p.lds, "sparse screen needs %zu bytes of LDS", p.lds);
     AR_TRY(ctx->sp_cand_s.reserve(sizeof(float) * (size_t)(p.n_grp * 8 * lut->n_chunks * 2 * CAND)));
     AR_TRY(ctx->sp_cand_i.reserve(sizeof(int32_t) * (size_t)(p.n_grp * 8 * lut->n_chunks * 2 * CAND)));
-    k_sparse_norm8<<<dim3((unsigned)p.n_grp, (unsigned)lut->n_win), 256, 0, s>>>(
+    k_sparse_norm8<<<dim3((unsigned)p.n_grp, (unsigned)lut->n_win), kNormThreads, 0, s>>>(
         images, n_roi, lut->n_win, lut->n_dir, p.slab, ctx->sp_inv.as<float>(), ctx->sp_half.as<uint32_t>());
     AR_HIP(hipGetLastError());
     AR_TRY(allow_lds(k_sparse_screen8<CAND>, p.lds));
