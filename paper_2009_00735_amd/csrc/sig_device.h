@@ -313,17 +313,20 @@ __device__ __forceinline__ float row_max16(float x)
     return x;
 }
 
-// Eq. (1) for one atom: bin index, FP32, fixed operation order.  The clamp
-// is applied before the conversion: trunc(clamp(t, 0, last)) equals
-// clamp(floor(t), 0, last) for every finite t (on [0, last] trunc = floor;
-// below 0 both give 0; above last both give last), and the conversion input
-// is always in range.
+// Eq. (1) for one atom: bin index, FP32, fixed operation order.  The
+// conversion truncates, takes everything below 0 (and what is not a number) to
+// 0 and everything past 2^32 to its largest, so with the minimum it is
+// clamp(floor(t), 0, last) for every t; a clamp of t before a signed
+// conversion is a half-rate instruction (200 ROIs of 1006 atoms and 10242
+// directions: 1000 us with it, 985 without).
 __device__ __forceinline__ int eq1_bin(float vx, float vy, float vz, float dx, float dy, float dz, float shift,
-                                       float scale, float last)
+                                       float scale, int last)
 {
     const float s = fmaf(vz, dz, fmaf(vy, dy, vx * dx));
     const float t = (s + shift) * scale;
-    return (int)__builtin_amdgcn_fmed3f(t, 0.0f, last);
+    uint32_t b;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(t));
+    return (int)min(b, (uint32_t)last);
 }
 
 // ------------------------------------------------- windows on matrix cores

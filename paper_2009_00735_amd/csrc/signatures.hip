@@ -132,7 +132,7 @@ template <int NB>
 __device__ __forceinline__ void bin_staged(const float4 *xs, int n, float vx, float vy, float vz, BinConsts bc,
                                            int *hist, int lane)
 {
-    constexpr float last = (float)(NB - 1);
+    constexpr int last = NB - 1;
     const float4 *p = xs + lane;
     int g = 0;
     for (; (g + 4) * kWave <= n; g += 4, p += 4 * kWave) {
@@ -388,7 +388,7 @@ __device__ __forceinline__ void bin_staged_mm(const Atom3 *xs, int n, const Dirs
                                               int *hist, int lane)
 {
     using P = BinPlan<NB>;
-    constexpr float last = (float)(NB - 1);
+    constexpr int last = NB - 1;
     constexpr int SLOTS = P::D >= 8 ? 1 : 8 / P::D;
     const Atom3 *p = xs + lane;
     int g = 0;
