@@ -231,7 +231,7 @@ def main():
     achieved_terms = terms_eval * evals / a10_s
     achieved_flops = terms_eval * (args.refine_steps * flop_per_term + flop_per_term_score) / a10_s
     roofline = {
-        "kernel": "k_sf_grad<4,2> (structure-factor adjoint, a10)",
+        "kernel": "k_sf<1,4> (structure-factor adjoint, a10)",
         "bound": "alu",
         "achieved": achieved_flops / 1e12,
         "peak": PEAK_FP32_VECTOR / 1e12,

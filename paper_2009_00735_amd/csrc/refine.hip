@@ -105,22 +105,33 @@ __device__ __forceinline__ void swap_acc(float &a, float &b)
 }
 
 // One atom's terms for one direction: the phases in turns, their sin and
-// cos, and the C and S sums.  (ax, ay, az) = f_kb u, so the dot product is
-// slot 0's phase; slot w's is g_w = f / f_kb times it.
-template <int NF>
+// cos, and the C and S sums (MODE 1: and P and Q).  (ax, ay, az) = f_kb u, so
+// the dot product is slot 0's phase; slot w's is g_w = f / f_kb times it.
+template <int MODE, int NF>
 __device__ __forceinline__ void sf_term(const float4 x, float ax, float ay, float az, const float (&g)[NF],
-                                        float (&C)[NF], float (&S)[NF])
+                                        float (&C)[NF], float (&S)[NF], float (&P)[NF][3], float (&Q)[NF][3])
 {
     const float d = fmaf(az, x.z, fmaf(ay, x.y, ax * x.x));
 #pragma unroll
     for (int w = 0; w < NF; ++w) {
         const float t = w == 0 ? d : g[w] * d;   // phase in turns
-        C[w] += __builtin_amdgcn_cosf(t);
-        S[w] += __builtin_amdgcn_sinf(t);
+        const float sn = __builtin_amdgcn_sinf(t);
+        const float cs = __builtin_amdgcn_cosf(t);
+        C[w] += cs;
+        S[w] += sn;
+        if (MODE == 1) {
+            P[w][0] = fmaf(x.x, sn, P[w][0]);
+            P[w][1] = fmaf(x.y, sn, P[w][1]);
+            P[w][2] = fmaf(x.z, sn, P[w][2]);
+            Q[w][0] = fmaf(x.x, cs, Q[w][0]);
+            Q[w][1] = fmaf(x.y, cs, Q[w][1]);
+            Q[w][2] = fmaf(x.z, cs, Q[w][2]);
+        }
     }
 }
 
-// MODE 0: score partials (the gradient slots zero); MODE 2: amplitudes.
+// MODE 0: score partials (the gradient slots zero); MODE 1: score and gradient
+// partials (the calls k_sf_grad does not take); MODE 2: amplitudes.
 // NF: number of frequencies (compile-time so the accumulators stay in VGPRs).
 // A last tile with fewer than kRemAtoms directions (e.g. the one direction
 // left after 20 full tiles of the 10242-node mesh's 5121 evaluated ones) is
@@ -137,7 +148,7 @@ __global__ __launch_bounds__(kTile) void k_sf(const float4 *__restrict__ rel, co
                                               float *__restrict__ partials, float *__restrict__ amp)
 {
     __shared__ float4 xs[kChunk];
-    __shared__ float red[kTile / 64];
+    __shared__ float red[kPartial][kTile / 64];
     // XCD-aware order: workgroup ids go round-robin to the 8 XCDs; item t =
     // (b % 8) * (grid / 8) + b / 8 keeps the tiles of one ROI on one XCD, so
     // its atoms come from HBM into that XCD's L2 once (grid padded to 8)
@@ -189,9 +200,12 @@ __global__ __launch_bounds__(kTile) void k_sf(const float4 *__restrict__ rel, co
         g[w] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gw)));
     }
     const float ax = fb * ux, ay = fb * uy, az = fb * uz;
-    float C[NF], S[NF];
+    float C[NF], S[NF], P[NF][3], Q[NF][3];
 #pragma unroll
-    for (int w = 0; w < NF; ++w) C[w] = S[w] = 0.f;
+    for (int w = 0; w < NF; ++w) {
+        C[w] = S[w] = 0.f;
+        P[w][0] = P[w][1] = P[w][2] = Q[w][0] = Q[w][1] = Q[w][2] = 0.f;
+    }
     const int64_t off0 = offsets[r];
     const int nw = (int)(offsets[r + 1] - off0);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -215,12 +229,14 @@ __global__ __launch_bounds__(kTile) void k_sf(const float4 *__restrict__ rel, co
         // groups (masks: 0x100 LDS read, 0x2 VALU, 0x400 transcendental):
         // both LDS reads, then per atom the dot product, a sin/cos pair,
         // the NF - 1 ratio multiplies, the other transcendentals and the
-        // 2 NF accumulations.
+        // accumulations (8 NF with the gradient, else 2 NF).  With the
+        // gradient at NF = 4: 4 % faster than one atom per iteration.
+        constexpr int kAcc = MODE == 1 ? 8 * NF : 2 * NF;
         int j = 0;
 #pragma unroll 1
         for (; j + 1 < n_run; j += 2) {
-            sf_term<NF>(xs[j], ax, ay, az, g, C, S);
-            sf_term<NF>(xs[j + 1], ax, ay, az, g, C, S);
+            sf_term<MODE, NF>(xs[j], ax, ay, az, g, C, S, P, Q);
+            sf_term<MODE, NF>(xs[j + 1], ax, ay, az, g, C, S, P, Q);
             __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
@@ -230,30 +246,44 @@ __global__ __launch_bounds__(kTile) void k_sf(const float4 *__restrict__ rel, co
                     __builtin_amdgcn_sched_group_barrier(0x2, NF - 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x400, 2 * NF - 2, 0);
                 }
-                __builtin_amdgcn_sched_group_barrier(0x2, 2 * NF, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, kAcc, 0);
             }
         }
-        if (j < n_run) sf_term<NF>(xs[j], ax, ay, az, g, C, S);
+        if (j < n_run) sf_term<MODE, NF>(xs[j], ax, ay, az, g, C, S, P, Q);
     }
 #pragma unroll
     for (int w = 1; w < NF; ++w) {   // slots back to frequency order
         if (w == kb) {
             swap_acc(C[0], C[w]);
             swap_acc(S[0], S[w]);
+            if (MODE == 1) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    swap_acc(P[0][c], P[w][c]);
+                    swap_acc(Q[0][c], Q[w][c]);
+                }
+            }
         }
     }
-    float J = 0.f;
-    sf_direction<MODE, NF>(C, S, nullptr, nullptr, f, nw, valid, v, vm, p, n_dir, targets, amp, r, J, nullptr);
+    float J = 0.f, gu[3] = {0.f, 0.f, 0.f};
+    sf_direction<MODE, NF>(C, S, P, Q, f, nw, valid, v, vm, p, n_dir, targets, amp, r, J, gu);
     if (MODE == 2) return;
+    const float part[kPartial] = {J,          gu[0] * nx, gu[0] * ny, gu[0] * nz, gu[1] * nx,
+                                  gu[1] * ny, gu[1] * nz, gu[2] * nx, gu[2] * ny, gu[2] * nz};
+    constexpr int kSums = MODE == 1 ? kPartial : 1;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) J += __shfl_xor(J, o);
-    if (lane == 0) red[wave] = J;
+    for (int k = 0; k < kSums; ++k) {
+        float x = part[k];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (lane == 0) red[k][wave] = x;
+    }
     __syncthreads();
     if (threadIdx.x < kPartial) {
         float x = 0.f;
 #pragma unroll
-        for (int w = 0; w < kTile / 64; ++w) x += red[w];
-        partials[((size_t)r * n_tiles + tile) * kPartial + threadIdx.x] = threadIdx.x == 0 ? x : 0.f;
+        for (int w = 0; w < kTile / 64; ++w) x += threadIdx.x < kSums ? red[threadIdx.x][w] : 0.f;
+        partials[((size_t)r * n_tiles + tile) * kPartial + threadIdx.x] = x;
     }
 }
 
@@ -974,8 +1004,21 @@ template <int MODE> SfFn sf_kernel(int n_freq)
     }
 }
 
-SfFn sf_grad_kernel(int n_freq)
+// The gradient's kernel for n_roi * n_tiles workgroups.  At one and four
+// frequencies k_sf<1,NF> forms the sums faster once every CU has several
+// workgroups after another: k_sf_grad's exchange of the sums costs a tile of
+// few atoms more, and its instruction mix no longer fills the gaps of a last
+// round.  us per evaluation (vector / matrix form) at 10242 directions and
+// four frequencies, 128, 256, 512 and 1000 ROIs: of 2000 atoms 1094 / 998,
+// 1904 / 1852, 3540 / 3574, 6612 / 6812; of 250 atoms 190 / 188, 302 / 324,
+// 526 / 604, 944 / 1126.  The line lies at 300 ROIs.  Two, three, six and
+// eight frequencies stay with k_sf_grad (600 ROIs of 850 atoms, 7, 4, 4 and
+// 6 % faster; one frequency 6 % slower).
+constexpr int64_t kVectorTiles = 12288;
+SfFn sf_grad_kernel(int n_freq, int64_t tiles)
 {
+    if (tiles >= kVectorTiles && n_freq == 1) return sf::k_sf<1, 1>;
+    if (tiles >= kVectorTiles && n_freq == 4) return sf::k_sf<1, 4>;
     switch (n_freq) {
     case 1: return sf::k_sf_grad<1, 2>;
     case 2: return sf::k_sf_grad<2, 2>;
@@ -1025,7 +1068,7 @@ static ar_status sf_launch_ws(int mode, const float *rel, const int64_t *offsets
         AR_HIP(hipGetLastError());
         return AR_OK;
     }
-    SfFn fn = mode == 1 ? sf_grad_kernel(n_freq) : sf_kernel<0>(n_freq);
+    SfFn fn = mode == 1 ? sf_grad_kernel(n_freq, n_roi * n_tiles) : sf_kernel<0>(n_freq);
     fn<<<blocks, sf::kTile, 0, s>>>((const float4 *)rel, offsets, quats, phase, n_phase, dirs, n_dir, rep, mate, n_eval,
                                     n_tiles, n_roi, freqs, targets, part, nullptr);
     AR_HIP(hipGetLastError());
