@@ -15,11 +15,11 @@
 // Membership is decided exactly as the paper's single-precision test:
 // fmaf(dz,dz,fmaf(dy,dy,dx*dx)) <= (float)(R*R).
 //
-// Measured on a tip of 2.8e6 atoms and 8000 ROIs (R = 2 nm): 0.48 ms per call,
-// where one wavefront per ROI walking its bounding cube, a second atomic pass
-// for the scatter and one thread per cell sorting took 0.97 ms; 300 ROIs in
-// 1.2e5 atoms 0.09 ms, 0.37.  Bound: the returning atomics of k_cell_keys
-// (0.14 ms), then the random reads of k_sorted_pos.
+// Measured on a tip of 2.8e6 atoms and 8000 ROIs (R = 2 nm): 0.37 ms per call,
+// 0.48 with the sort by global atomics, and 0.97 where one wavefront per ROI
+// walked its bounding cube, a second atomic pass scattered and one thread per
+// cell sorted; 300 ROIs in 1.2e5 atoms 0.09 ms, 0.37.  Bound: the two passes
+// over the ROIs' rows (0.17 ms), then the sort's passes over its records.
 #include <math.h>
 
 #include <algorithm>
@@ -65,6 +65,14 @@ __global__ __launch_bounds__(1024) void k_centre_bbox(const float *__restrict__ 
 
 __device__ __forceinline__ int cell_coord(float p, float o, float inv_h) { return (int)floorf((p - o) * inv_h); }
 
+// Cell id of an atom, ncells outside the grid.
+__device__ __forceinline__ uint32_t cell_key(float x, float y, float z, const Grid &g)
+{
+    const int cx = cell_coord(x, g.ox, g.inv_h), cy = cell_coord(y, g.oy, g.inv_h), cz = cell_coord(z, g.oz, g.inv_h);
+    const bool in = cx >= 0 && cx < g.nx && cy >= 0 && cy < g.ny && cz >= 0 && cz < g.nz;
+    return in ? (uint32_t)(cx + g.nx * (cy + g.ny * cz)) : (uint32_t)g.nx * g.ny * g.nz;
+}
+
 __global__ __launch_bounds__(256) void k_fill_i32(int32_t *__restrict__ a, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -80,13 +88,9 @@ __global__ __launch_bounds__(256) void k_cell_keys(const float *__restrict__ pos
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const uint32_t ncells = (uint32_t)g.nx * g.ny * g.nz;
-    int cx = cell_coord(pos[3 * i + 0], g.ox, g.inv_h);
-    int cy = cell_coord(pos[3 * i + 1], g.oy, g.inv_h);
-    int cz = cell_coord(pos[3 * i + 2], g.oz, g.inv_h);
-    bool in = cx >= 0 && cx < g.nx && cy >= 0 && cy < g.ny && cz >= 0 && cz < g.nz;
-    const uint32_t key = in ? (uint32_t)(cx + g.nx * (cy + g.ny * cz)) : ncells;
+    const uint32_t key = cell_key(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], g);
     keys[i] = key;
-    if (in) slot[i] = atomicAdd(&counts[key], 1);
+    if (key < ncells) slot[i] = atomicAdd(&counts[key], 1);
 }
 
 // Each atom inside the grid, with its cell, to its slot.
@@ -123,6 +127,109 @@ __global__ __launch_bounds__(256) void k_sorted_pos(const float *__restrict__ po
 #pragma unroll 8
     for (int j = s0; j < s1; ++j) rank += idx[j].x < v.x ? 1 : 0;
     out[s0 + rank] = p;
+}
+
+// ---------------------------------------------- the sort by parts
+// The same sorted positions for many atoms: the cells fall into at most kParts
+// runs of 2^shift, the atoms go to their run (counts per workgroup, one scan,
+// a scatter of position and index), and a workgroup per run counts and
+// places its atoms by cell in LDS.  Bound: the passes over the 16-byte
+// records; the form above is bound by its global atomics, 7e9 a second
+// (k_cell_keys), and the random reads of k_sorted_pos.
+constexpr int kParts = 512;
+constexpr int kPartAtoms = 4096;                 // atoms per workgroup of the first two passes
+constexpr int kPartCells = 8192;                 // cells of a run, in LDS
+constexpr int64_t kPartMin = 262144;             // atoms
+
+// SCATTER == false: counts[part][workgroup]; true: the records to their places.
+template <bool SCATTER>
+__global__ __launch_bounds__(kParts) void k_part(const float *__restrict__ pos, int64_t n, Grid g, int shift,
+                                                 int n_parts, int32_t *__restrict__ counts,
+                                                 const int32_t *__restrict__ start, float4 *__restrict__ rec)
+{
+    __shared__ int h[kParts];
+    const int tid = threadIdx.x;
+    const int64_t at = (int64_t)tid * gridDim.x + blockIdx.x;
+    h[tid] = SCATTER && tid < n_parts ? start[at] : 0;
+    __syncthreads();
+    const uint32_t ncells = (uint32_t)g.nx * g.ny * g.nz;
+#pragma unroll
+    for (int k = 0; k < kPartAtoms / kParts; ++k) {
+        const int64_t i = (int64_t)blockIdx.x * kPartAtoms + k * kParts + tid;
+        if (i >= n) break;
+        const float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
+        const uint32_t key = cell_key(x, y, z, g);
+        if (key >= ncells) continue;
+        const int slot = atomicAdd(&h[key >> shift], 1);
+        if (SCATTER) rec[slot] = make_float4(x, y, z, __int_as_float((int)i));
+    }
+    if (SCATTER) return;
+    __syncthreads();
+    if (tid < n_parts) counts[at] = h[tid];
+}
+
+// One run of cells: cell starts, and its records by cell (in any order).
+__global__ __launch_bounds__(1024) void k_part_cells(const float4 *__restrict__ rec, const int32_t *__restrict__ start,
+                                                     int n_wg, int n_parts, Grid g, int shift,
+                                                     int32_t *__restrict__ cell_start, float4 *__restrict__ out)
+{
+    __shared__ int cnt[kPartCells];
+    __shared__ int wave_sum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t ncells = (uint32_t)g.nx * g.ny * g.nz, k0 = blockIdx.x << shift;
+    const int nc = (int)min(1u << shift, ncells - k0);
+    const int base = start[(int64_t)blockIdx.x * n_wg], end = start[((int64_t)blockIdx.x + 1) * n_wg];
+    for (int c = tid; c < kPartCells; c += 1024) cnt[c] = 0;
+    __syncthreads();
+    for (int i = base + tid; i < end; i += 1024) {
+        const float4 a = rec[i];
+        atomicAdd(&cnt[min(cell_key(a.x, a.y, a.z, g) - k0, (uint32_t)nc - 1)], 1);
+    }
+    __syncthreads();
+    constexpr int PER = kPartCells / 1024;
+    int v[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) sum += v[k] = cnt[tid * PER + k];
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int run = base + incl - sum;
+    for (int w = 0; w < wave; ++w) run += wave_sum[w];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int c = tid * PER + k;
+        cnt[c] = run;
+        if (c < nc) cell_start[k0 + c] = run;
+        run += v[k];
+    }
+    if (tid == 0 && (int)blockIdx.x == n_parts - 1) cell_start[ncells] = end;
+    __syncthreads();
+    for (int i = base + tid; i < end; i += 1024) {
+        const float4 a = rec[i];
+        out[atomicAdd(&cnt[min(cell_key(a.x, a.y, a.z, g) - k0, (uint32_t)nc - 1)], 1)] = a;
+    }
+}
+
+// Records to their rank in the cell by atom index, as k_sorted_pos.
+__global__ __launch_bounds__(256) void k_part_rank(const float4 *__restrict__ rec, const int32_t *__restrict__ types,
+                                                   const int32_t *__restrict__ cell_start, Grid g,
+                                                   float4 *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t ncells = (uint32_t)g.nx * g.ny * g.nz;
+    if (i >= cell_start[ncells]) return;
+    const float4 p = rec[i];
+    const uint32_t key = min(cell_key(p.x, p.y, p.z, g), ncells - 1);
+    const int a = __float_as_int(p.w), s0 = cell_start[key], s1 = cell_start[key + 1];
+    int rank = 0;
+#pragma unroll 8
+    for (int j = s0; j < s1; ++j) rank += __float_as_int(rec[j].w) < a ? 1 : 0;
+    out[s0 + rank] = make_float4(p.x, p.y, p.z, __int_as_float(types ? types[a] : 0));
 }
 
 // Atom type t is accepted iff 0 <= t < 64 and bit t of the mask is set.
@@ -380,12 +487,41 @@ static ar_status gather_sort(ar_context *ctx, const float *positions, const int3
     // counting sort of the atoms by cell: counts and slots, cell starts
     // (exclusive scan), scatter, per-cell input order
     const int64_t n = n_atoms;
+    AR_TRY(ctx->g_cell_start.reserve(sizeof(int32_t) * ((size_t)ncells + 1)));
+    AR_TRY(ctx->g_sorted.reserve(sizeof(float4) * (n + 1)));
+    // by parts from 262144 atoms on (2.8e6 atoms 0.16 ms, the form below 0.28; at 1.2e5
+    // both 0.04), where a run of cells fits LDS
+    if (n >= kPartMin && ncells <= (uint32_t)kParts * kPartCells) {
+        int shift = 0;
+        while ((ncells - 1) >> shift >= (uint32_t)kParts) ++shift;
+        const int n_parts = (int)((ncells - 1) >> shift) + 1;
+        const int n_wg = (int)((n + kPartAtoms - 1) / kPartAtoms);
+        const int64_t n_counts = (int64_t)n_parts * n_wg;
+        AR_TRY(ctx->g_slot.reserve(sizeof(int32_t) * n_counts));
+        AR_TRY(ctx->g_counts32.reserve(sizeof(int32_t) * (n_counts + 1)));
+        AR_TRY(ctx->g_keys.reserve(sizeof(float4) * n));
+        AR_TRY(ctx->g_vals.reserve(sizeof(float4) * n));
+        AR_TRY(ctx->g_temp.reserve(std::max(sizeof(int32_t) * scan::tiles(n_counts), sizeof(int64_t) * scan::tiles(n_roi)) +
+                                   16));
+        int32_t *counts = ctx->g_slot.as<int32_t>(), *start = ctx->g_counts32.as<int32_t>();
+        float4 *rec = ctx->g_keys.as<float4>(), *by_cell = ctx->g_vals.as<float4>();
+        k_part<false><<<n_wg, kParts, 0, stream>>>(positions, n, g, shift, n_parts, counts, nullptr, nullptr);
+        AR_HIP(hipGetLastError());
+        AR_TRY((scan::exclusive_scan<int32_t, int32_t>(counts, n_counts, start, ctx->g_temp.as<int32_t>(), stream)));
+        k_part<true><<<n_wg, kParts, 0, stream>>>(positions, n, g, shift, n_parts, nullptr, start, rec);
+        AR_HIP(hipGetLastError());
+        k_part_cells<<<n_parts, 1024, 0, stream>>>(rec, start, n_wg, n_parts, g, shift,
+                                                   ctx->g_cell_start.as<int32_t>(), by_cell);
+        AR_HIP(hipGetLastError());
+        k_part_rank<<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(by_cell, types, ctx->g_cell_start.as<int32_t>(), g,
+                                                                     ctx->g_sorted.as<float4>());
+        AR_HIP(hipGetLastError());
+        return AR_OK;
+    }
     AR_TRY(ctx->g_keys.reserve(sizeof(uint32_t) * (n + 1)));
     AR_TRY(ctx->g_slot.reserve(sizeof(int32_t) * (n + 1)));
     AR_TRY(ctx->g_vals.reserve(sizeof(int2) * (n + 1)));
     AR_TRY(ctx->g_counts32.reserve(sizeof(int32_t) * ((size_t)ncells + 1)));
-    AR_TRY(ctx->g_cell_start.reserve(sizeof(int32_t) * ((size_t)ncells + 1)));
-    AR_TRY(ctx->g_sorted.reserve(sizeof(float4) * (n + 1)));
     AR_TRY(ctx->g_temp.reserve(std::max(sizeof(int32_t) * scan::tiles(ncells), sizeof(int64_t) * scan::tiles(n_roi)) +
                                16));
     int32_t *counts = ctx->g_counts32.as<int32_t>();

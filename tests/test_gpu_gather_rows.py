@@ -83,6 +83,27 @@ def test_cells_of_a_hundred_thousand_atoms_keep_the_input_order():
     check(pos[gen.permutation(len(pos))], gen.uniform(0.2, 0.4, (3, 3)).astype(f32), 0.9)
 
 
+@pytest.mark.parametrize("n", [262143, 262144, 262145, 300001])
+@pytest.mark.parametrize("shape", ["box", "crowd", "few cells", "many cells"])
+def test_sort_by_parts(n, shape):
+    """Either side of the line between the two sorts: even and crowded cells,
+    fewer cells than parts, a part's most cells and beyond, types."""
+    gen = np.random.default_rng(n)
+    pos, R = gen.uniform(-8, 8, (n, 3)), 1.1
+    centres = gen.uniform(-8, 8, (40, 3))
+    if shape == "crowd":
+        pos[: n // 8] = gen.normal(1.0, 0.05, (n // 8, 3))
+        pos = pos[gen.permutation(n)]
+    elif shape == "few cells":
+        R, centres = 4.0, gen.uniform(-1, 1, (5, 3))
+    elif shape == "many cells":
+        R, centres = 0.22 if n % 2 else 0.1, gen.uniform(-8, 8, (40, 3))
+    pos, centres = pos.astype(f32), centres.astype(f32)
+    check(pos, centres, R, sample=range(0, len(centres), 4))
+    types = gen.integers(-1, 70, n).astype(np.int32)
+    check(pos, centres, R, types, (1 << 63) | 0b1011, range(0, len(centres), 9))
+
+
 def test_more_rois_than_row_counts_are_kept_for():
     gen = np.random.default_rng(4)
     pos = gen.uniform(-3, 3, (5000, 3)).astype(f32)
