@@ -6,7 +6,8 @@
 // ROI centres +- R; atoms are bucketed by cell with a counting sort (per-cell
 // counts by atomics whose return value is the atom's slot in its cell, an
 // exclusive scan for the cell starts, a scatter, then each cell's atoms ranked
-// by their index, so the result is the stable sort by cell id).  Rows of cells
+// by their index, so the result is the stable sort by cell id; many atoms are
+// counted and placed in LDS by runs of cells instead).  Rows of cells
 // are contiguous in the sorted array, so each row is one coalesced range.  A
 // ROI is served by one workgroup: its wavefronts take the rows its ball
 // reaches in turn, each row cut to the ball's chord (with slack against FP32

@@ -14,8 +14,9 @@
 // gfx950 design: one workgroup per (ROI, 256-direction tile); the ROI's
 // relative coordinates are staged in LDS (broadcast reads: every lane of a
 // wave reads the same atom), each lane owns one direction and all
-// frequencies (score and amplitudes, k_sf; the gradient's sums go to the
-// matrix cores, k_sf_grad), sin/cos by the hardware transcendental unit (v_sin_f32 and
+// frequencies (score and amplitudes, and the gradient of large calls, k_sf;
+// the gradient's sums of the others go to the matrix cores, k_sf_grad),
+// sin/cos by the hardware transcendental unit (v_sin_f32 and
 // v_cos_f32 take the phase in turns, so f * (u . x) needs no 2 pi and no
 // range reduction for |f u.x| < 256).  Per-tile partial sums (J and the
 // 3x3 G) are reduced across tiles in a fixed order by a second kernel, so
