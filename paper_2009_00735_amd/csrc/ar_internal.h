@@ -5,6 +5,7 @@
 #include <stdarg.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <map>
 #include <memory>
 #include <string>
@@ -148,6 +149,18 @@ ar_status gather_rois(ar_context *ctx, const float *positions, const int32_t *ty
                       int32_t *counts, bool want_big, hipStream_t stream,
                       RoiUse use);
 constexpr size_t kHostBytes = 256;
+// A grid holds fewer than 2^32 work items along x; a larger one is not refused
+// but wraps around and leaves rows unwritten.  launch(r0, count) for the n rows
+// in as many parts as that needs, `threads` work items per row.
+template <class F> ar_status by_rows(int64_t n, int64_t threads, F &&launch)
+{
+    const int64_t most = (int64_t)UINT32_MAX / threads;
+    for (int64_t r0 = 0; r0 < n; r0 += most) {
+        launch(r0, (unsigned)std::min(most, n - r0));
+        AR_HIP(hipGetLastError());
+    }
+    return AR_OK;
+}
 struct MeshCells;
 // cube-map nearest-node candidate lists of `dirs` in ctx->m_cells (mesh.hip)
 ar_status build_mesh_cells(ar_context *ctx, const float *dirs, int n_dir, hipStream_t stream, MeshCells &mc);

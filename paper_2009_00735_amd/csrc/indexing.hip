@@ -713,22 +713,16 @@ ar_status launch_rescore(ar_context *ctx, const float *images, const ar_library 
 {
     const size_t stage = sizeof(float) * (size_t)lib->n_dir;
     constexpr int W = kRescoreWaves;
-    if (stage + 4096 <= (size_t)ctx->lds_per_block) {
-        if (stage > 65536)   // on every launch: the attribute belongs to the current device
-            AR_HIP(hipFuncSetAttribute((const void *)k_rescore<CAND, true, W>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)stage));
-        k_rescore<CAND, true, W><<<(unsigned)n_roi, 64 * W, stage, s>>>(images, ctx->i_inv.as<float>(), lib->ref,
-                                                                  lib->inv_max.as<float>(),
-                                                                  ctx->i_merge_idx.as<int32_t>(), lib->n_win,
-                                                                  lib->n_dir, lib->n_lib, k, top_idx, top_score);
-    } else {
-        k_rescore<CAND, false, W><<<(unsigned)n_roi, 64 * W, 0, s>>>(images, ctx->i_inv.as<float>(), lib->ref,
-                                                               lib->inv_max.as<float>(),
-                                                               ctx->i_merge_idx.as<int32_t>(), lib->n_win,
-                                                               lib->n_dir, lib->n_lib, k, top_idx, top_score);
-    }
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    const bool staged = stage + 4096 <= (size_t)ctx->lds_per_block;
+    const auto fn = staged ? k_rescore<CAND, true, W> : k_rescore<CAND, false, W>;
+    if (staged && stage > 65536)   // on every launch: the attribute belongs to the current device
+        AR_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)stage));
+    return by_rows(n_roi, 64 * W, [&](int64_t r0, unsigned n) {
+        fn<<<n, 64 * W, staged ? stage : 0, s>>>(
+            images + (size_t)r0 * lib->n_win * lib->n_dir, ctx->i_inv.as<float>() + r0 * lib->n_win, lib->ref,
+            lib->inv_max.as<float>(), ctx->i_merge_idx.as<int32_t>() + r0 * CAND, lib->n_win, lib->n_dir, lib->n_lib, k,
+            top_idx + r0 * k, top_score + r0 * k);
+    });
 }
 
 // Orientation and phase of library entries idx[i] (-1 or out of range: NaN
@@ -837,9 +831,10 @@ int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 ar_status normalise_cast(const float *img, int64_t n, int64_t n_pad, int n_win, int n_dir, int64_t Kp, float *inv,
                          uint16_t *out, hipStream_t s)
 {
-    k_normalise_cast<<<dim3((unsigned)n_pad, (unsigned)n_win), 256, 0, s>>>(img, n, n_win, n_dir, Kp, inv, out);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    return by_rows(n_pad, 256, [&](int64_t r0, unsigned rows) {
+        k_normalise_cast<<<dim3(rows, (unsigned)n_win), 256, 0, s>>>(img + (size_t)r0 * n_win * n_dir, n - r0, n_win, n_dir,
+                                                                     Kp, inv + r0 * n_win, out + (size_t)r0 * Kp);
+    });
 }
 
 // Correlation (main and optional tail launch), merge, FP32 rescore and the

@@ -933,20 +933,16 @@ ar_status merge_rescore(ar_context *ctx, const ar_sparse_lut *lut, const float *
     AR_HIP(hipGetLastError());
     // stage each ROI window in LDS when n_dir floats fit beside the static arrays
     const size_t stage = sizeof(float) * (size_t)lut->n_dir;
-    if (stage + 4096 <= (size_t)ctx->lds_per_block) {
-        AR_TRY(allow_lds(k_sparse_rescore<CAND, true>, stage));
-        k_sparse_rescore<CAND, true><<<(unsigned)n_roi, 64 * kRescoreWaves, stage, s>>>(
-            images, ctx->sp_inv.as<float>(), lut->n_win, lut->n_dir, lut->cseg.as<int32_t>(),
-            lut->sval_w.as<float>(), lut->lut_gi.as<uint16_t>(), lut->n_hat, lut->phase_start.as<int64_t>(),
-            lut->n_phase, lut->n_lib, ctx->sp_merge.as<int32_t>(), k, top_idx, top_score);
-    } else {
-        k_sparse_rescore<CAND, false><<<(unsigned)n_roi, 64 * kRescoreWaves, 0, s>>>(
-            images, ctx->sp_inv.as<float>(), lut->n_win, lut->n_dir, lut->cseg.as<int32_t>(),
-            lut->sval_w.as<float>(), lut->lut_gi.as<uint16_t>(), lut->n_hat, lut->phase_start.as<int64_t>(),
-            lut->n_phase, lut->n_lib, ctx->sp_merge.as<int32_t>(), k, top_idx, top_score);
-    }
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    const bool staged = stage + 4096 <= (size_t)ctx->lds_per_block;
+    const auto fn = staged ? k_sparse_rescore<CAND, true> : k_sparse_rescore<CAND, false>;
+    if (staged) AR_TRY(allow_lds(fn, stage));
+    return by_rows(n_roi, 64 * kRescoreWaves, [&](int64_t r0, unsigned n) {
+        fn<<<n, 64 * kRescoreWaves, staged ? stage : 0, s>>>(
+            images + (size_t)r0 * lut->n_win * lut->n_dir, ctx->sp_inv.as<float>() + r0 * lut->n_win, lut->n_win,
+            lut->n_dir, lut->cseg.as<int32_t>(), lut->sval_w.as<float>(), lut->lut_gi.as<uint16_t>(), lut->n_hat,
+            lut->phase_start.as<int64_t>(), lut->n_phase, lut->n_lib, ctx->sp_merge.as<int32_t>() + r0 * CAND, k,
+            top_idx + r0 * k, top_score + r0 * k);
+    });
 }
 
 // RB ROIs per group (8 for the 8-bit screen): workspace and launch shape.

@@ -1,0 +1,47 @@
+"""Batches past 2^22 ROIs, where a kernel of 1024 threads per ROI would need
+more work items than one grid holds (2^32): every call still answers, each ROI
+as in a small batch."""
+import pytest
+import torch
+
+from paper_2009_00735_amd import native as nat
+from paper_2009_00735_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def repeated(a, n):
+    """The rows of a over and over, n of them."""
+    return a.repeat((-(-n // len(a)), *[1] * (a.dim() - 1)))[:n].contiguous()
+
+
+def assert_repeats(got, want):
+    whole = len(got) // len(want) * len(want)
+    assert bool((got[:whole].view(-1, *want.shape) == want).all())
+    assert torch.equal(got[whole:], want[:len(got) - whole])
+
+
+@pytest.mark.parametrize("n_roi", [2 ** 22 + 3, 2 ** 24 - 1])
+def test_dense_indexing(n_roi):
+    gen = torch.Generator(device="cuda").manual_seed(n_roi)
+    ctx = nat.Context(0)
+    refs = torch.rand((40, 1, 12), generator=gen, device="cuda")
+    rois = torch.rand((61, 1, 12), generator=gen, device="cuda")
+    lib = nat.Library(ctx, refs)
+    want = nat.index_orientations(ctx, rois, lib, 2)
+    got = nat.index_orientations(ctx, repeated(rois, n_roi), lib, 2)
+    for g, w in zip(got, want):
+        assert_repeats(g, w)
+
+
+def test_sparse_indexing():
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    ctx = nat.Context(0)
+    dirs = torch.from_numpy(synth.icosphere(0)).cuda()
+    quats = torch.randn((50, 4), generator=gen, device="cuda", dtype=torch.float64)
+    lut = nat.SparseLUT(ctx, torch.rand((1, 1, 12), generator=gen, device="cuda"), dirs, quats, [50], 8)
+    rois = torch.rand((61, 1, 12), generator=gen, device="cuda")
+    want = nat.index_orientations_sparse(ctx, rois, lut, 2)
+    got = nat.index_orientations_sparse(ctx, repeated(rois, 2 ** 22 + 3), lut, 2)
+    for g, w in zip(got, want):
+        assert_repeats(g, w)
