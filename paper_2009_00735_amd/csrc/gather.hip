@@ -609,7 +609,11 @@ ar_status gather_csr(ar_context *ctx, const float *positions, const int32_t *typ
 // and rows of storage (64 MiB), and no workgroup walks more than 32 blocks of
 // 1024 atoms.  Sorting costs a dozen launches and a second wait whatever its
 // size (75 us for one ROI of 1 nm); the tests take 5 to 20 us at these bounds.
-static bool small_gather(int64_t n_atoms, int64_t n_roi) { return n_atoms <= 32768 && n_atoms * n_roi <= (1 << 22); }
+// Hardly any atoms leave the ROIs: 1024 threads each have to fit one grid.
+static bool small_gather(int64_t n_atoms, int64_t n_roi)
+{
+    return n_atoms <= 32768 && n_atoms * n_roi <= (1 << 22) && n_roi <= (int64_t)UINT32_MAX / 1024;
+}
 
 ar_status gather_rois(ar_context *ctx, const float *positions, const int32_t *types, int64_t n_atoms,
                       const float *centres, int64_t n_roi, float radius, const uint64_t *type_masks, int n_masks,

@@ -1,6 +1,7 @@
 """Batches past 2^22 ROIs, where a kernel of 1024 threads per ROI would need
 more work items than one grid holds (2^32): every call still answers, each ROI
 as in a small batch."""
+import numpy as np
 import pytest
 import torch
 
@@ -43,5 +44,20 @@ def test_sparse_indexing():
     rois = torch.rand((61, 1, 12), generator=gen, device="cuda")
     want = nat.index_orientations_sparse(ctx, rois, lut, 2)
     got = nat.index_orientations_sparse(ctx, repeated(rois, 2 ** 22 + 3), lut, 2)
+    for g, w in zip(got, want):
+        assert_repeats(g, w)
+
+
+@pytest.mark.parametrize("n_atoms,n_roi", [(0, 2 ** 22 + 1), (1, 2 ** 22)])
+def test_signatures_of_hardly_any_atoms(n_atoms, n_roi):
+    gen = np.random.default_rng(n_atoms)
+    dirs = gen.normal(size=(3, 3))
+    dirs = torch.from_numpy((dirs / np.linalg.norm(dirs, axis=1, keepdims=True)).astype(np.float32)).cuda()
+    pos = torch.zeros((n_atoms, 3), device="cuda")
+    base = torch.tensor([[0.1, 0.2, 0.0], [9.0, 0.0, 0.0], [0.0, -0.4, 0.3]], device="cuda")
+    ctx = nat.Context(0)
+    want = nat.araullo_signatures(ctx, pos, base, 1.0, dirs, 256, [[8, 12]])
+    assert want[1].tolist() == [n_atoms, 0, n_atoms]
+    got = nat.araullo_signatures(ctx, pos, repeated(base, n_roi), 1.0, dirs, 256, [[8, 12]])
     for g, w in zip(got, want):
         assert_repeats(g, w)
