@@ -374,7 +374,10 @@ template <int NB> struct BinPlan {
     static constexpr int TW = N2 == 4 ? 4 : N2 / 2;   // outer factors per lane
     static_assert(NB >= 256 && NB <= 2048, "16, 8, 4 or 2 directions per pass");
 };
-constexpr int kSpan = 61440;   // most atoms in the histograms at once (a multiple of every stage, below 65536)
+// Most atoms in the histograms at once.  Spans start at its multiples, so what
+// they add up, and in which order, does not depend on the stage.
+constexpr int kSpan = 61440;
+static_assert(kSpan < 65536, "a 16-bit half counts them");
 
 // Per-lane tables, loaded once per kernel; k = the lane's bin (lane % 32).
 template <int NB> struct BinTables {

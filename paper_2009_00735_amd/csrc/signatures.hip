@@ -505,26 +505,21 @@ __device__ __forceinline__ void process_item_mm(const float4 *__restrict__ rel, 
         Dirs<D> u;
         if (active) {
             u.load(dirs, v, v1);
-            zero_hist_mm<NB>(hist, lane);
             clear_spectra<NB>(x);
         }
-        int held = 0;   // atoms in the histograms
-        for (int c0 = 0; c0 < nw; c0 += cap) {
-            const int n = min(cap, nw - c0);
-            __syncthreads();
-            stage_atoms(xs, rel, off0 + c0, n);
-            __syncthreads();
-            if (!active) continue;
-            if (held + n > kSpan) {
-                add_spectra<NB>(hist, t, lane, large, x);
-                zero_hist_mm<NB>(hist, lane);
-                held = 0;
+        for (int s0 = 0; s0 < nw; s0 += kSpan) {
+            const int s1 = s0 + min(kSpan, nw - s0);
+            if (active) zero_hist_mm<NB>(hist, lane);
+            for (int c0 = s0; c0 < s1; c0 += cap) {
+                const int n = min(cap, s1 - c0);
+                __syncthreads();
+                stage_atoms(xs, rel, off0 + c0, n);
+                __syncthreads();
+                if (active) bin_staged_mm<NB>(xs, n, u, bc, hist, lane);
             }
-            bin_staged_mm<NB>(xs, n, u, bc, hist, lane);
-            held += n;
+            if (active) add_spectra<NB>(hist, t, lane, large, x);
         }
         if (active) {
-            add_spectra<NB>(hist, t, lane, large, x);
             finish_pass<NB>(x, scratch, t, ws, lane, r, v, v1, n_dir, images);
         }
     }
