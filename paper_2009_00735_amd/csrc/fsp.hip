@@ -15,13 +15,17 @@
 //
 // Matrix cores: each FP32 factor is split into two FP16 parts, x = hi + lo
 // (22 bits), and a product of two factors is hi hi + hi lo + lo hi on
-// v_mfma_f32_32x32x16_f16, exact products accumulated in FP32; the dropped
-// lo lo is at most 2^-22 of the product, below the rounding of the factors'
-// own sine and cosine.  Three FP16 MFMAs replace one FP32 product at sixteen
-// times its rate.  The phases are formed and reduced to [-1/2, 1/2] turns in
-// FP64, where an FP32 phase of up to 20 turns was most of the error.
-// Measured against 64 bits (relative 2-norm, 256 ROIs of 2016 and 2836 atoms,
-// L = 64): 4.7e-7, where the FP32 matrix form with FP32 phases had 1.4e-6.
+// v_mfma_f32_32x32x16_f16, exact products accumulated in FP32.  Both parts
+// are rounded to nearest, so |lo| <= 2^-11 |x| and the dropped lo lo is at most
+// 2^-22 of the product, of either sign.  (With hi cut toward zero it reaches
+// 2^-20 and always has the product's sign, which does not average out over the
+// atoms: amplitudes on average 0.77 2^-22 too small, now 0.39, with FP32
+// factors 0.27; the conversions cost the same.)  Three FP16 MFMAs replace one
+// FP32 product at sixteen times its rate.  The phases are formed and reduced to
+// [-1/2, 1/2] turns in FP64, where an FP32 phase of up to 20 turns was most of
+// the error.  Measured against 64 bits (relative 2-norm, 256 ROIs of 2016 and
+// 2836 atoms, L = 64): 4.3e-7, where the FP32 matrix form with FP32 phases had
+// 1.4e-6.
 //
 // octant_item: a workgroup of 8 wavefronts takes 16 a, 16 b and 32 c; a wavefront
 // one tile of 32 pairs (2 a by 16 b).  Per 32 atoms it forms the factors once
@@ -48,6 +52,7 @@ namespace fsp {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
@@ -62,13 +67,13 @@ __device__ __forceinline__ float2 unit(double turns)
     return make_float2(__builtin_amdgcn_cosf(f), __builtin_amdgcn_sinf(f));
 }
 
-// Two values split in FP16, x = hi + lo: the high parts rounded toward zero
-// in one instruction, each remainder x - hi formed and rounded in one more
+// Two values split in FP16, x = hi + lo: the high parts rounded to nearest in
+// one instruction, each remainder x - hi formed and rounded in one more
 // (v_fma_mixlo_f16, v_fma_mixhi_f16).  `minus` is -1, kept from the compiler:
 // a plain subtraction is not fused with the two conversions.
 __device__ __forceinline__ void split2(float x0, float x1, float minus, uint32_t &hi, uint32_t &lo)
 {
-    const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(x0, x1));
+    const f16x2 h = __builtin_convertvector((f32x2{x0, x1}), f16x2);
     f16x2 l;
     l.x = (_Float16)fmaf((float)h.x, minus, x0);
     l.y = (_Float16)fmaf((float)h.y, minus, x1);
