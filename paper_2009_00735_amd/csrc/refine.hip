@@ -1025,10 +1025,10 @@ template <int MODE> SfFn sf_kernel(int n_freq)
 // eight frequencies stay with k_sf_grad (600 ROIs of 850 atoms, 7, 4, 4 and
 // 6 % faster; one frequency 6 % slower).
 constexpr int64_t kVectorTiles = 12288;
+bool sf_vector_form(int n_freq, int64_t tiles) { return tiles >= kVectorTiles && (n_freq == 1 || n_freq == 4); }
 SfFn sf_grad_kernel(int n_freq, int64_t tiles)
 {
-    if (tiles >= kVectorTiles && n_freq == 1) return sf::k_sf<1, 1>;
-    if (tiles >= kVectorTiles && n_freq == 4) return sf::k_sf<1, 4>;
+    if (sf_vector_form(n_freq, tiles)) return n_freq == 1 ? sf::k_sf<1, 1> : sf::k_sf<1, 4>;
     switch (n_freq) {
     case 1: return sf::k_sf_grad<1, 2>;
     case 2: return sf::k_sf_grad<2, 2>;
@@ -1234,11 +1234,14 @@ ar_status ar_refine_orientations(ar_context *ctx, const float *rel, const int64_
     ar::sf::k_copy4<<<(unsigned)((4 * n_roi + 255) / 256), 256, 0, s>>>(quats, trial, n_roi);
     AR_HIP(hipGetLastError());
     AR_TRY(ar::eval_list(ctx, directions, n_dir, s));
+    // The last evaluation only decides whether its trial is accepted: score
+    // alone (the forward kernel, about half the adjoint's work), where that
+    // forms the same sums as the evaluations it is compared with.
+    const int64_t tiles = n_roi * ((n_dir + ar::sf::kTile - 1) / ar::sf::kTile);
+    const int last_mode = steps == 0 || ar::sf_vector_form(n_freq, tiles) ? 0 : 1;
     for (int it = 0; it <= steps; ++it) {
-        // the last evaluation only decides whether its trial is accepted:
-        // score alone (the forward kernel, about half the adjoint's work)
         const bool last = it == steps;
-        AR_TRY(ar::sf_launch(ctx, last ? 0 : 1, rel, offsets, n_roi, trial, phase, n_phase, directions, n_dir, freqs, targets,
+        AR_TRY(ar::sf_launch(ctx, last ? last_mode : 1, rel, offsets, n_roi, trial, phase, n_phase, directions, n_dir, freqs, targets,
                              n_freq, Jt, gt, nullptr, s, true));
         ar::sf::k_refine_update<<<nb, 256, 0, s>>>(st, trial, Jt, last ? nullptr : gt, n_roi, it == 0 ? 1 : 0, a0);
         AR_HIP(hipGetLastError());
