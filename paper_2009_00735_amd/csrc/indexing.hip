@@ -837,8 +837,6 @@ ar_status normalise_cast(const float *img, int64_t n, int64_t n_pad, int n_win, 
     });
 }
 
-// Correlation (main and optional tail launch), merge, FP32 rescore and the
-// optional copy of the BF16-stage candidates, for CAND candidates per row.
 // Which correlation a call takes by default; fewer than 256 of the 256 x 256
 // tiles leave CUs idle, the smaller forms are less efficient per tile.  Counted
 // in tiles per CU (256 CUs); us per call of 1000 ROIs and 10242 directions
@@ -850,15 +848,25 @@ ar_status normalise_cast(const float *img, int64_t n, int64_t n_pad, int n_win, 
 //                   per CU (4000 rows) 1118 against 940 for 128 x 128
 //   128 x 128       at most 1 per CU: 4000 rows 1428 / 940 / 1191
 //   128 x 256       at most 1 per CU: 8000 rows 1474 / 1275 / 1311 (256 x 128)
+// Rows count as they are launched, in whole tiles.  The 128 x 256 tile leaves
+// four candidate lists per row and 256 library rows, the 256 x 256 tile two (one
+// for 32 candidates), and one wavefront merges a row's lists: with one or two
+// row blocks that costs more than the tile gains, the more the longer the
+// library and the shorter K.  256 x 256 / 128 x 256, 100 ROIs: 16 candidates,
+// 65000 rows of K = 2568 331 / 383, 10248 564 / 592, 20484 895 / 877; 36000 rows
+// of 2568 244 / 247, 5128 336 / 333; 32 candidates, 52000 rows of 10248 892 /
+// 998, 20484 1230 / 1226.  The line follows those crossings.  Lists of 64 are a
+// wavefront's, one per segment: 65000 rows of 2568 1067 / 590.
 // All of them give the same scores, and so the same candidates.
 enum class CorrForm { tiles, half, quarter, wave64, wave32 };
-CorrForm corr_form(int64_t n_roi, int64_t n_pad, int64_t cus)
+CorrForm corr_form(int64_t n_roi, int64_t n_pad, int64_t Kp, int cand, int64_t cus)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return (n_roi + bm - 1) / bm * (n_pad / bn); };
     if (tiles(32, 32) <= 2 * cus || (n_roi <= 32 && tiles(32, 32) <= 8 * cus)) return CorrForm::wave32;
     if (tiles(64, 64) <= 3 * cus) return CorrForm::wave64;
     if (tiles(128, 128) <= cus) return CorrForm::quarter;
-    return tiles(128, 256) <= cus ? CorrForm::half : CorrForm::tiles;
+    const bool merges_pay = cand == 64 || n_pad / 256 <= 112 + Kp / (cand == 32 ? 256 : 128);
+    return tiles(128, 256) <= cus && merges_pay ? CorrForm::half : CorrForm::tiles;
 }
 
 template <int T, int STAGES>
@@ -876,6 +884,8 @@ ar_status launch_wave(ar_context *ctx, const ar_library *lib, int64_t rows, floa
     return AR_OK;
 }
 
+// Correlation (main and optional tail launch), merge, FP32 rescore and the
+// optional copy of the BF16-stage candidates, for CAND candidates per row.
 template <int CAND>
 ar_status run_index(ar_context *ctx, CorrForm form, int64_t rows, const CorrCfg &cfg, const CorrCfg &tail_cfg, bool split, const CorrLaunch &main_l,
                     const CorrLaunch &tail_l, int n_lists, const float *images, const ar_library *lib, int64_t n_roi,
@@ -1041,15 +1051,20 @@ ar_status index_orientations_ex(ar_context *ctx, const float *images, int64_t n_
     // per segment) 166.1-167.7 / 159.9-160.3; 2500 x 100000 (16) 20.5-20.6
     // / 18.7; 5000 x 20000 (7) 10.5 / 9.8; 10000 x 40000 (5) 33.7-33.8 /
     // 34.2; 20000 x 12500 (2) 27.6-27.8 / 28.0.
-    const int64_t m_pad = idx::round_up(n_roi, idx::kPadM);
     const idx::CorrForm form =
-        ctx->corr_tile_set ? idx::CorrForm::tiles : idx::corr_form(n_roi, lib->n_pad, ctx->cu_count);
+        ctx->corr_tile_set ? idx::CorrForm::tiles : idx::corr_form(n_roi, lib->n_pad, lib->Kp, cand, ctx->cu_count);
     idx::CorrCfg cfg = ctx->corr_tile_set ? idx::CorrCfg{ctx->corr_waves, ctx->corr_wtm, ctx->corr_wtn, ctx->corr_bk}
                        : form == idx::CorrForm::quarter ? idx::CorrCfg{4, 2, 2, idx::kBK}
                        : form == idx::CorrForm::half    ? idx::CorrCfg{8, 2, 2, idx::kBK}
                        : cand >= 32                     ? idx::CorrCfg{4, 4, 4, idx::kBK}
                                                         : idx::CorrCfg{8, 4, 2, idx::kBK};
-    const int m_blocks = (int)(m_pad / cfg.bm());
+    // rows with padding: to the tile's own height, which is what corr_form
+    // counted (to 256 whatever the tile, half of the workgroups of 100 ROIs
+    // worked on padding: 40000 references of 2562 directions 620 us, now 460)
+    const int64_t rows = idx::round_up(n_roi, form == idx::CorrForm::wave32   ? 32
+                                              : form == idx::CorrForm::wave64 ? 64
+                                                                              : cfg.bm());
+    const int m_blocks = (int)((rows + cfg.bm() - 1) / cfg.bm());
     const int n_tiles = (int)(lib->n_pad / cfg.bn());
     // segments: a workgroup walks tiles_per_seg column tiles of one row block.
     // The makespan is rounds of resident workgroups times tiles per
@@ -1115,16 +1130,13 @@ ar_status index_orientations_ex(ar_context *ctx, const float *images, int64_t n_
                         (split ? tail_l.n_seg * idx::lists_per_row(cand, tail_cfg.threads(), tail_cfg.bm()) : 0);
     main_l.list_stride = tail_l.list_stride = n_lists;
 
-    const int64_t rows = form == idx::CorrForm::wave32   ? idx::round_up(n_roi, 32)
-                         : form == idx::CorrForm::wave64 ? idx::round_up(n_roi, 64)
-                                                         : m_pad;   // with padding
     AR_TRY(ctx->i_bf16.reserve(sizeof(uint16_t) * (size_t)rows * lib->Kp));
     AR_TRY(ctx->i_inv.reserve(sizeof(float) * (size_t)n_roi * lib->n_win));
     if (form == idx::CorrForm::wave32 || form == idx::CorrForm::wave64) {
         AR_TRY(ctx->i_cand_score.reserve(sizeof(float) * (size_t)rows * lib->n_pad));
     } else {
-        AR_TRY(ctx->i_cand_score.reserve(sizeof(float) * (size_t)m_pad * n_lists * cand));
-        AR_TRY(ctx->i_cand_idx.reserve(sizeof(int32_t) * (size_t)m_pad * n_lists * cand));
+        AR_TRY(ctx->i_cand_score.reserve(sizeof(float) * (size_t)rows * n_lists * cand));
+        AR_TRY(ctx->i_cand_idx.reserve(sizeof(int32_t) * (size_t)rows * n_lists * cand));
     }
     AR_TRY(ctx->i_merge_idx.reserve(sizeof(int32_t) * (size_t)n_roi * cand));
 
