@@ -371,7 +371,7 @@ ar_status index_orientations_sparse(ar_context *ctx, const float *images, int64_
  *   L             multiple of 32 in [32, 512]
  *   k_max         > 0 (the grid covers [-k_max, k_max - dk] per axis)
  *   amp           device float [n_roi][L][L][L], out
- * AR_EINVAL if the launch would exceed 2^31 - 1 workgroups (n_roi times
+ * AR_EINVAL if the call would need 2^31 - 1 workgroups or more (n_roi times
  * (L/32)^2 ceil(L/64) + 3 ceil(L/64)^2 / 8 + 3 L / 32, about).  Does not
  * synchronise.
  */

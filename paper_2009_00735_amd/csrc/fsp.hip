@@ -444,13 +444,19 @@ ar_status ar_fsp_amplitudes(ar_context *ctx, const float *rel, const int64_t *of
     const int nt = L / 32, ht = (L / 2 + 31) / 32, kw = ar::fsp::kWaves;
     ar::fsp::Plan pl{n_roi, L, 3 * ht * ht, nt * nt * ht, (3 * L - 2 + ar::fsp::kLine - 1) / ar::fsp::kLine, 0, 0};
     AR_CHECK(n_roi < (int64_t)INT32_MAX, "too many ROIs per call (%lld)", (long long)n_roi);
-    pl.face_blocks = (n_roi * pl.tiles + kw - 1) / kw;
-    pl.octant_blocks = n_roi * pl.per;
-    const int64_t blocks = pl.face_blocks + pl.octant_blocks + (n_roi * pl.items + kw - 1) / kw;
-    AR_CHECK(blocks < (int64_t)INT32_MAX, "too many workgroups (%lld): index fewer ROIs per call", (long long)blocks);
-    ar::fsp::k_fsp<<<(unsigned)blocks, ar::fsp::kThreads, 0, s>>>((const float4 *)rel, offsets, pl, dk, amp);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    auto blocks = [&](int64_t n) {
+        pl.n_roi = n;
+        pl.face_blocks = (n * pl.tiles + kw - 1) / kw;
+        pl.octant_blocks = n * pl.per;
+        return pl.face_blocks + pl.octant_blocks + (n * pl.items + kw - 1) / kw;
+    };
+    AR_CHECK(blocks(n_roi) < (int64_t)INT32_MAX, "too many workgroups (%lld): index fewer ROIs per call",
+             (long long)blocks(n_roi));
+    return ar::by_rows(n_roi, ar::fsp::kThreads * (blocks(kw) / kw + 1), [&](int64_t r0, unsigned n) {
+        const unsigned grid = (unsigned)blocks(n);
+        ar::fsp::k_fsp<<<grid, ar::fsp::kThreads, 0, s>>>((const float4 *)rel, offsets + r0, pl, dk,
+                                                          amp + (size_t)r0 * L * L * L);
+    });
 }
 
 }  // extern "C"

@@ -61,3 +61,27 @@ def test_signatures_of_hardly_any_atoms(n_atoms, n_roi):
     got = nat.araullo_signatures(ctx, pos, repeated(base, n_roi), 1.0, dirs, 256, [[8, 12]])
     for g, w in zip(got, want):
         assert_repeats(g, w)
+
+
+def test_reciprocal_grids():
+    """1920000 grids of L = 32 fill most of the card's memory (252 GB)."""
+    n_roi, L = 1920000, 32
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < n_roi * L ** 3 * 4 + 2 ** 32:
+        pytest.skip("needs 256 GB of free device memory")
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    rows = [3, 0, 1, 2]
+    rel = torch.rand((6, 4), generator=gen, device="cuda")
+    first = torch.tensor([0, 3, 3, 4], device="cuda")
+    off = (first + 6 * torch.arange(n_roi // 4, device="cuda")[:, None]).flatten()
+    off = torch.cat([off, torch.tensor([6 * (n_roi // 4)], device="cuda")])
+    ctx = nat.Context(0)
+    want = nat.ar_fsp_amplitudes(ctx, rel, off[:5].contiguous(), L, 10.0)
+    assert want[:, L // 2, L // 2, L // 2].tolist() == pytest.approx(rows)
+    out = torch.empty((n_roi, L, L, L), device="cuda")
+    out[:, 0, 0, 0] = out[:, -1, -1, -1] = -1.0
+    nat.ar_fsp_amplitudes(ctx, rel.repeat(n_roi // 4, 1), off, L, 10.0, out=out)
+    for part in out.view(-1, 4, L, L, L).split(4000):
+        assert bool((part == want).all())
+    del out, part
+    torch.cuda.empty_cache()
