@@ -154,7 +154,7 @@ constexpr size_t kHostBytes = 256;
 // in as many parts as that needs, `threads` work items per row.
 template <class F> ar_status by_rows(int64_t n, int64_t threads, F &&launch)
 {
-    const int64_t most = (int64_t)UINT32_MAX / threads;
+    const int64_t most = std::max<int64_t>((int64_t)UINT32_MAX / threads, 1);
     for (int64_t r0 = 0; r0 < n; r0 += most) {
         launch(r0, (unsigned)std::min(most, n - r0));
         AR_HIP(hipGetLastError());

@@ -110,10 +110,11 @@ ar_status ar_rotate_reference(ar_context *ctx, const float *reference, int32_t n
     AR_CHECK((n + 255) / 256 < (int64_t)INT32_MAX, "too many items");
     ar::MeshCells mc;
     AR_TRY(ar::build_mesh_cells(ctx, directions, n_dir, (hipStream_t)stream, mc));
-    ar::k_rotate_reference<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
-        reference, n_win, directions, n_dir, quats, phase, n_phase, n_lib, mc, out);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    return ar::by_rows(n_lib, 2 * (int64_t)n_dir, [&](int64_t l0, unsigned rows) {
+        ar::k_rotate_reference<<<(unsigned)(((int64_t)rows * n_dir + 255) / 256), 256, 0, (hipStream_t)stream>>>(
+            reference, n_win, directions, n_dir, quats + 4 * l0, phase + l0, n_phase, rows, mc,
+            out + (size_t)l0 * n_win * n_dir);
+    });
 }
 
 }  // extern "C"

@@ -1066,26 +1066,22 @@ static ar_status sf_launch_ws(int mode, const float *rel, const int64_t *offsets
 {
     const int32_t *rep = list + n_dir, *mate = list + 2 * n_dir, *n_eval = list + 3 * n_dir;
     const int n_tiles = (n_dir + sf::kTile - 1) / sf::kTile;
-    const unsigned blocks = (unsigned)((n_roi * n_tiles + 7) / 8 * 8);   // k_sf: a multiple of the 8 XCDs
-    if (mode == 2) {
-        sf_kernel<2>(n_freq)<<<blocks, sf::kTile, 0, s>>>((const float4 *)rel, offsets, quats, phase, n_phase, dirs, n_dir,
-                                                          rep, mate, n_eval, n_tiles, n_roi, freqs, targets, nullptr,
-                                                          amp);
-        AR_HIP(hipGetLastError());
-        sf_rem_kernel<2>(n_freq)<<<(unsigned)n_roi, sf::kTile, 0, s>>>((const float4 *)rel, offsets, quats, phase,
-                                                                       n_phase, dirs, n_dir, rep, mate, n_eval, n_tiles,
-                                                                       freqs, targets, nullptr, amp);
-        AR_HIP(hipGetLastError());
-        return AR_OK;
-    }
-    SfFn fn = mode == 1 ? sf_grad_kernel(n_freq, n_roi * n_tiles) : sf_kernel<0>(n_freq);
-    fn<<<blocks, sf::kTile, 0, s>>>((const float4 *)rel, offsets, quats, phase, n_phase, dirs, n_dir, rep, mate, n_eval,
-                                    n_tiles, n_roi, freqs, targets, part, nullptr);
-    AR_HIP(hipGetLastError());
-    SfRemFn fr = mode == 1 ? sf_rem_kernel<1>(n_freq) : sf_rem_kernel<0>(n_freq);
-    fr<<<(unsigned)n_roi, sf::kTile, 0, s>>>((const float4 *)rel, offsets, quats, phase, n_phase, dirs, n_dir, rep, mate,
-                                             n_eval, n_tiles, freqs, targets, part, nullptr);
-    AR_HIP(hipGetLastError());
+    const SfFn fn = mode == 2   ? sf_kernel<2>(n_freq)
+                    : mode == 1 ? sf_grad_kernel(n_freq, n_roi * n_tiles)
+                                : sf_kernel<0>(n_freq);
+    const SfRemFn fr = mode == 2   ? sf_rem_kernel<2>(n_freq)
+                       : mode == 1 ? sf_rem_kernel<1>(n_freq)
+                                   : sf_rem_kernel<0>(n_freq);
+    AR_TRY(by_rows(n_roi, 2 * (int64_t)n_tiles * sf::kTile, [&](int64_t r0, unsigned n) {
+        const unsigned blocks = (unsigned)(((int64_t)n * n_tiles + 7) / 8 * 8);   // k_sf: a multiple of the 8 XCDs
+        float *p = part ? part + (size_t)r0 * n_tiles * sf::kPartial : nullptr;
+        float *a = amp ? amp + (size_t)r0 * n_freq * n_dir : nullptr;
+        fn<<<blocks, sf::kTile, 0, s>>>((const float4 *)rel, offsets + r0, quats + 4 * r0, phase + r0, n_phase, dirs,
+                                        n_dir, rep, mate, n_eval, n_tiles, n, freqs, targets, p, a);
+        fr<<<n, sf::kTile, 0, s>>>((const float4 *)rel, offsets + r0, quats + 4 * r0, phase + r0, n_phase, dirs, n_dir,
+                                   rep, mate, n_eval, n_tiles, freqs, targets, p, a);
+    }));
+    if (mode == 2) return AR_OK;
     sf::k_sf_reduce<<<(unsigned)((n_roi + 15) / 16), 256, 0, s>>>(part, n_tiles, n_roi, quats, score,
                                                                     mode == 1 ? grad : nullptr);
     AR_HIP(hipGetLastError());
@@ -1203,9 +1199,11 @@ ar_status ar_sf_score_f64(ar_context *ctx, const float *rel, const int64_t *offs
     const int n_tiles = (n_dir + ar::sf::kTile - 1) / ar::sf::kTile;
     AR_TRY(ctx->r_partials.reserve(sizeof(double) * (size_t)n_roi * n_tiles));
     double *part = ctx->r_partials.as<double>();
-    ar::sf::k_sf_f64<<<(unsigned)(n_roi * n_tiles), ar::sf::kTile, 0, s>>>(
-        (const float4 *)rel, offsets, quats, phase, n_phase, directions, n_dir, n_tiles, freqs, targets, n_freq, part);
-    AR_HIP(hipGetLastError());
+    AR_TRY(ar::by_rows(n_roi, (int64_t)n_tiles * ar::sf::kTile, [&](int64_t r0, unsigned n) {
+        ar::sf::k_sf_f64<<<n * (unsigned)n_tiles, ar::sf::kTile, 0, s>>>(
+            (const float4 *)rel, offsets + r0, quats + 4 * r0, phase + r0, n_phase, directions, n_dir, n_tiles, freqs,
+            targets, n_freq, part + r0 * n_tiles);
+    }));
     ar::sf::k_sf_reduce_f64<<<(unsigned)((n_roi + 255) / 256), 256, 0, s>>>(part, n_tiles, n_roi, score);
     AR_HIP(hipGetLastError());
     return AR_OK;

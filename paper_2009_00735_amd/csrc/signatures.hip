@@ -709,11 +709,12 @@ ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets
                       : mm  ? sig::plain_kernel_mm(log2i(nbins))
                             : sig::plain_kernel<false>(log2i(nbins));
     AR_TRY(sig::allow_lds(fn, lds));
-    fn<<<(unsigned)blocks, sig::kWaves * 64, lds, stream>>>((const float4 *)rel, offsets, ostride, directions, n_dir,
-                                                           dirs_per_block, n_tiles, W, bc, ws, cap, images, hist,
-                                                           amp);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    return by_rows(n_roi, (int64_t)n_tiles * sig::kWaves * 64, [&](int64_t r0, unsigned n) {
+        auto from = [&](auto *p, int64_t row) { return p ? p + (size_t)r0 * n_dir * row : p; };
+        fn<<<n * (unsigned)n_tiles, sig::kWaves * 64, lds, stream>>>(
+            (const float4 *)rel, offsets + r0 * ostride, ostride, directions, n_dir, dirs_per_block, n_tiles, W, bc, ws,
+            cap, from(images, ws.n), from(hist, nbins), from(amp, nbins / 2 + 1));
+    });
 }
 
 }  // namespace ar

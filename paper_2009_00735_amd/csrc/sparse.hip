@@ -1250,14 +1250,18 @@ ar_status index_orientations_sparse(ar_context *ctx, const float *images, int64_
     AR_HIP(hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
     const int sc = lut->screen;
-    if (k <= 16) {
-        if (sc == 8) return sparse::run_screen8<16>(ctx, lut, images, n_roi, k, top_idx, top_score, s);
-        if (sc == 2) return sparse::run_screen<2, 16>(ctx, lut, images, n_roi, k, top_idx, top_score, s);
-        return sparse::run_screen<1, 16>(ctx, lut, images, n_roi, k, top_idx, top_score, s);
-    }
-    if (sc == 8) return sparse::run_screen8<32>(ctx, lut, images, n_roi, k, top_idx, top_score, s);
-    if (sc == 2) return sparse::run_screen<2, 32>(ctx, lut, images, n_roi, k, top_idx, top_score, s);
-    return sparse::run_screen<1, 32>(ctx, lut, images, n_roi, k, top_idx, top_score, s);
+    const auto run = k <= 16 ? (sc == 8   ? sparse::run_screen8<16>
+                                : sc == 2 ? sparse::run_screen<2, 16>
+                                          : sparse::run_screen<1, 16>)
+                             : (sc == 8   ? sparse::run_screen8<32>
+                                : sc == 2 ? sparse::run_screen<2, 32>
+                                          : sparse::run_screen<1, 32>);
+    // one screen's workgroups, rounded up to the 8 XCDs, in one grid (by_rows)
+    const int64_t most = sc * std::max<int64_t>(((int64_t)UINT32_MAX / sparse::kThreads - 8) / lut->n_chunks, 1);
+    for (int64_t r0 = 0; r0 < n_roi; r0 += most)
+        AR_TRY(run(ctx, lut, images + (size_t)r0 * lut->n_win * lut->n_dir, std::min(most, n_roi - r0), k,
+                   top_idx + r0 * k, top_score + r0 * k, s));
+    return AR_OK;
 }
 
 }  // extern "C"

@@ -1,6 +1,5 @@
-"""Batches past 2^22 ROIs, where a kernel of 1024 threads per ROI would need
-more work items than one grid holds (2^32): every call still answers, each ROI
-as in a small batch."""
+"""Batches whose kernels need more work items than one grid holds (2^32; past it
+a grid wraps around): every call still answers, each ROI as in a small batch."""
 import numpy as np
 import pytest
 import torch
@@ -35,20 +34,21 @@ def test_dense_indexing(n_roi):
         assert_repeats(g, w)
 
 
-def test_sparse_indexing():
+@pytest.mark.parametrize("n_lib,n_roi", [(50, 2 ** 22 + 3), (20000, 3355443)])   # ten chunks: 419431 groups
+def test_sparse_indexing(n_lib, n_roi):
     gen = torch.Generator(device="cuda").manual_seed(1)
     ctx = nat.Context(0)
     dirs = torch.from_numpy(synth.icosphere(0)).cuda()
-    quats = torch.randn((50, 4), generator=gen, device="cuda", dtype=torch.float64)
-    lut = nat.SparseLUT(ctx, torch.rand((1, 1, 12), generator=gen, device="cuda"), dirs, quats, [50], 8)
+    quats = torch.randn((n_lib, 4), generator=gen, device="cuda", dtype=torch.float64)
+    lut = nat.SparseLUT(ctx, torch.rand((1, 1, 12), generator=gen, device="cuda"), dirs, quats, [n_lib], 8)
     rois = torch.rand((61, 1, 12), generator=gen, device="cuda")
     want = nat.index_orientations_sparse(ctx, rois, lut, 2)
-    got = nat.index_orientations_sparse(ctx, repeated(rois, 2 ** 22 + 3), lut, 2)
+    got = nat.index_orientations_sparse(ctx, repeated(rois, n_roi), lut, 2)
     for g, w in zip(got, want):
         assert_repeats(g, w)
 
 
-@pytest.mark.parametrize("n_atoms,n_roi", [(0, 2 ** 22 + 1), (1, 2 ** 22)])
+@pytest.mark.parametrize("n_atoms,n_roi", [(0, 2 ** 22 + 1), (1, 2 ** 22), (1, 2 ** 24 + 5)])
 def test_signatures_of_hardly_any_atoms(n_atoms, n_roi):
     gen = np.random.default_rng(n_atoms)
     dirs = gen.normal(size=(3, 3))
@@ -61,6 +61,45 @@ def test_signatures_of_hardly_any_atoms(n_atoms, n_roi):
     got = nat.araullo_signatures(ctx, pos, repeated(base, n_roi), 1.0, dirs, 256, [[8, 12]])
     for g, w in zip(got, want):
         assert_repeats(g, w)
+
+
+def test_structure_factors():
+    n_roi = 2 ** 24 + 9
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    dirs = torch.randn((3, 3), generator=gen, device="cuda")
+    dirs = dirs / dirs.norm(dim=1, keepdim=True)
+    rel = torch.rand((3, 4), generator=gen, device="cuda")
+    off = torch.tensor([0, 2, 2], device="cuda") + 3 * torch.arange(-(-n_roi // 3), device="cuda")[:, None]
+    off = torch.cat([off.flatten(), torch.tensor([3 * len(off)], device="cuda")])[:n_roi + 1].contiguous()
+    rel = rel.repeat(-(-n_roi // 3), 1)
+    q = torch.randn((3, 4), generator=gen, device="cuda")
+    phase = torch.zeros(n_roi, dtype=torch.int32, device="cuda")
+    f, T = torch.tensor([[4.0]], device="cuda"), torch.rand((1, 1, 3), generator=gen, device="cuda")
+    ctx = nat.Context(0)
+
+    def calls(n):
+        a = (ctx, rel, off[:n + 1].contiguous(), repeated(q, n), phase[:n].contiguous(), dirs, f)
+        s64 = nat.ar_sf_score_f64(*a[:3], a[3].double(), *a[4:6], f.double(), T.double())
+        return *nat.ar_sf_score_grad(*a, T), nat.ar_sf_score_grad(*a, T, grad=False)[0], nat.ar_sf_amplitudes(*a), s64
+
+    small, large = calls(3), calls(n_roi)
+    for i, (g, w) in enumerate(zip(large, small)):
+        if i < 2:   # past the line between the gradient's two forms: last bits
+            assert torch.allclose(g[:3], w, rtol=1e-3, atol=1e-3 * float(w.abs().max()))
+            w = g[:3]
+        assert_repeats(g, w)
+
+
+def test_rotated_references():
+    n_lib = 2 ** 32 // 10242 + 5
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    dirs = torch.from_numpy(synth.icosphere(5)).cuda()
+    ref = torch.rand((1, 1, len(dirs)), generator=gen, device="cuda")
+    q = torch.randn((3, 4), generator=gen, device="cuda", dtype=torch.float64)
+    ctx = nat.Context(0)
+    phase = torch.zeros(n_lib, dtype=torch.int32, device="cuda")
+    want = nat.ar_rotate_reference(ctx, ref, dirs, q, phase[:3].contiguous())
+    assert_repeats(nat.ar_rotate_reference(ctx, ref, dirs, repeated(q, n_lib), phase), want)
 
 
 def test_reciprocal_grids():
