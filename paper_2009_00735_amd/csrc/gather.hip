@@ -500,12 +500,12 @@ static ar_status gather_sort(ar_context *ctx, const float *positions, const int3
         const int64_t n_counts = (int64_t)n_parts * n_wg;
         AR_TRY(ctx->g_slot.reserve(sizeof(int32_t) * n_counts));
         AR_TRY(ctx->g_counts32.reserve(sizeof(int32_t) * (n_counts + 1)));
-        AR_TRY(ctx->g_keys.reserve(sizeof(float4) * n));
         AR_TRY(ctx->g_vals.reserve(sizeof(float4) * n));
         AR_TRY(ctx->g_temp.reserve(std::max(sizeof(int32_t) * scan::tiles(n_counts), sizeof(int64_t) * scan::tiles(n_roi)) +
                                    16));
         int32_t *counts = ctx->g_slot.as<int32_t>(), *start = ctx->g_counts32.as<int32_t>();
-        float4 *rec = ctx->g_keys.as<float4>(), *by_cell = ctx->g_vals.as<float4>();
+        // the records by run lie where the sorted atoms go in the end: 32 bytes per atom in all
+        float4 *rec = ctx->g_sorted.as<float4>(), *by_cell = ctx->g_vals.as<float4>();
         k_part<false><<<n_wg, kParts, 0, stream>>>(positions, n, g, shift, n_parts, counts, nullptr, nullptr);
         AR_HIP(hipGetLastError());
         AR_TRY((scan::exclusive_scan<int32_t, int32_t>(counts, n_counts, start, ctx->g_temp.as<int32_t>(), stream)));
