@@ -203,7 +203,9 @@ ar_status ar_signature_plan_tune(ar_plan *plan, const float *rel, const int64_t 
 /* Chosen configuration (any out pointer may be NULL): directions per work
  * item, atoms per LDS stage, workgroups launched per compute unit, and the
  * register form (1: as allocated, 4: at most 128 VGPRs per lane so four
- * wavefronts share a SIMD). */
+ * wavefronts share a SIMD).  The register form is that of the FFT kernels, which
+ * serve windows spanning more than 32 bins; narrower ones of up to 2048 bins
+ * have one form whatever it says. */
 ar_status ar_signature_plan_config(const ar_plan *plan, int32_t *dirs_per_item,
                                    int32_t *atoms_per_stage, int32_t *blocks_per_cu,
                                    int32_t *min_waves);

@@ -52,6 +52,8 @@ template <int LOGNB> struct LaneConsts {
     static constexpr int NB = 1 << LOGNB;
     static constexpr int NC = NB / 2;
     static constexpr int R_LAST = FftPlan<NC>::R_LAST;
+    // windows within 32 bins come here with 4096 bins only (use_mm)
+    static constexpr bool kSplit = LOGNB == 12;
     PassTwiddles<NB, 8> tw8;
     PassTwiddles<NB, 64> tw64;
     float2 ftw[R_LAST - 1];   // w^(t k), w = exp(-2 pi i / NC), k = this lane's bin
@@ -86,7 +88,7 @@ template <int LOGNB> struct LaneConsts {
     {
         if constexpr (FftPlan<NC>::NS_LAST > 8) tw8.load(Wg, lane);
         if constexpr (FftPlan<NC>::NS_LAST > 64) tw64.load(Wg, lane);
-        if (ws.rows == 2) load_split(Wg, min(ws.kmin + (lane & 31), ws.kmax), lane >= 32);
+        if (kSplit && ws.rows == 2) load_split(Wg, min(ws.kmin + (lane & 31), ws.kmax), lane >= 32);
         else load_bin(Wg, min(ws.kmin + lane, ws.kmax));
         // row w = lane / 16 reads window w, bin lo_w + min(lane % 16, width - 1)
         rd = 0;
@@ -192,8 +194,11 @@ __device__ __forceinline__ void finish_direction(float *A, LaneConsts<LOGNB> &lc
     fft_head<NB, NC, 1, true>(Z, lc.tw8, lc.tw64, lane);
     wave_lds_sync();
     if (ws.rows) {
-        scratch[lane] = ws.rows == 2 ? bin_amplitude_split<NC>(Z, lc.mmx, lc.ftw, lc.wk)
-                                     : bin_amplitude<NC>(Z, lc.mm1, lc.mm2, lc.ftw, lc.wk);
+        if constexpr (LaneConsts<LOGNB>::kSplit)
+            scratch[lane] = ws.rows == 2 ? bin_amplitude_split<NC>(Z, lc.mmx, lc.ftw, lc.wk)
+                                         : bin_amplitude<NC>(Z, lc.mm1, lc.mm2, lc.ftw, lc.wk);
+        else
+            scratch[lane] = bin_amplitude<NC>(Z, lc.mm1, lc.mm2, lc.ftw, lc.wk);
         wave_lds_sync();
         const float m = row_max16(scratch[lc.rd]);
         const int w = lane >> 4;
