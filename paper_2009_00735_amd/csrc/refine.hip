@@ -298,13 +298,6 @@ __global__ __launch_bounds__(kTile) void k_sf(const float4 *__restrict__ rel, co
 // sin = h + l (22 bits), and columns [1, x_h, y_h, z_h, x_l, y_l, z_l] of the
 // scaled coordinates, so that (h + l) times every column is exact products.
 //
-// Error: what the parts leave, 2^-23 of a sine and 2^-25 of the ROI's largest
-// coordinate per term, is far below that of the phases, of up to 20 turns.  So
-// the directions f R n are formed in FP64 and rounded once: against 64 bits
-// (six frequency counts, ROIs of 60 to 2000 atoms) J 4.6e-8 and the gradient
-// 2.3e-4 off, k_sf, whose directions go through FP32 steps, 5.6e-8 and 6.1e-4,
-// these sums with FP32 directions 5.7e-8 and 6.2e-4.  The time is the same.
-//
 // Bound: the vector unit.  Of about 170 cycles per atom and 64 directions at
 // four frequencies the eight sines and cosines take 70 (8.6 each, measured);
 // splitting a value takes 9.6 (two conversions for two values and a mixed
@@ -349,7 +342,6 @@ template <int NF, int G> struct SfStage {
     _Float16 tab[kCols][kChunk + 32];                        // columns 1, hi, lo; rows 64 bytes apart in the banks
     float ex[kTile / 64][16 * NF * kRowF];                   // D exchange, one region per wavefront
     float red[kPartial][kTile / 64];
-    double rot[9];                                           // the ROI's rotation matrix
 };
 
 template <int NF, int G>
@@ -377,6 +369,9 @@ __global__ __launch_bounds__(kTile) void k_sf_grad(const float4 *__restrict__ re
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, part16 = lane >> 4;
     const int p = min(max(phase[r], 0), n_phase - 1);   // out-of-range phases are clamped
+    float q[4] = {quats[4 * r], quats[4 * r + 1], quats[4 * r + 2], quats[4 * r + 3]};
+    float M[9];
+    rotation(q, M);
     float f[NF];
 #pragma unroll
     for (int w = 0; w < NF; ++w) f[w] = freqs[p * NF + w];
@@ -395,10 +390,6 @@ __global__ __launch_bounds__(kTile) void k_sf_grad(const float4 *__restrict__ re
     }
     const int64_t off0 = offsets[r];
     const int nw = (int)(offsets[r + 1] - off0);
-    if (tid == 0) {
-        const double q[4] = {quats[4 * r], quats[4 * r + 1], quats[4 * r + 2], quats[4 * r + 3]};
-        rotation(q, st.rot);
-    }
     // the coordinates' scale: a power of two that brings the largest below
     // one, so that neither FP16 part overflows and the parts of the largest
     // hold 22 bits
@@ -431,11 +422,11 @@ __global__ __launch_bounds__(kTile) void k_sf_grad(const float4 *__restrict__ re
         for (int u = 0; u < G; ++u) {
             const int i = d0 + 16 * u + row;
             const int v = i < n_eval ? rep[i] : 0;
-            const double nx = i < n_eval ? dirs[3 * v] : 0.f, ny = i < n_eval ? dirs[3 * v + 1] : 0.f,
-                         nz = i < n_eval ? dirs[3 * v + 2] : 0.f;
-            ax[u] = (float)(fb * (st.rot[0] * nx + st.rot[1] * ny + st.rot[2] * nz));
-            ay[u] = (float)(fb * (st.rot[3] * nx + st.rot[4] * ny + st.rot[5] * nz));
-            az[u] = (float)(fb * (st.rot[6] * nx + st.rot[7] * ny + st.rot[8] * nz));
+            const float nx = i < n_eval ? dirs[3 * v] : 0.f, ny = i < n_eval ? dirs[3 * v + 1] : 0.f,
+                        nz = i < n_eval ? dirs[3 * v + 2] : 0.f;
+            ax[u] = fb * (M[0] * nx + M[1] * ny + M[2] * nz);
+            ay[u] = fb * (M[3] * nx + M[4] * ny + M[5] * nz);
+            az[u] = fb * (M[6] * nx + M[7] * ny + M[8] * nz);
         }
         f32x4 sn[G][NF], cs[G][NF];
 #pragma unroll
