@@ -450,9 +450,8 @@ ar_status ar_rotate_reference(ar_context *ctx, const float *reference, int32_t n
  *   freqs         device float [n_phase][n_freq]
  *   targets       device float [n_phase][n_freq][n_dir]
  *   score         device float [n_roi], out
- *   grad          device float [n_roi][4] or NULL, out (NULL: forward only;
- *                 a score formed beside a gradient may differ from the one
- *                 formed alone in its last bits, about 1e-7 of it)
+ *   grad          device float [n_roi][4] or NULL, out (NULL: forward only,
+ *                 the score is the same)
  * n_freq in [1, 8].  Domain: the phase f_w (u_v . x_j), in turns, goes to
  * the hardware sine and cosine without range reduction, which are specified
  * for |phase| <= 256 turns; their argument carries a rounding error of about
@@ -511,8 +510,8 @@ ar_status ar_sf_amplitudes(ar_context *ctx, const float *rel, const int64_t *off
  * q' = normalise(q - a g/|g|) is accepted iff J(q') <= J(q) - 1e-4 a |g|,
  * then a grows by 1.5; otherwise a halves and q stays.  steps + 1
  * evaluations at the trial points of all ROIs (the first at the start):
- * J and its gradient, the last only for its J.  All J of a call are formed
- * in the same way, as ar_sf_score_grad forms them beside a gradient.
+ * J and its gradient, except the last, which only decides acceptance and
+ * takes J alone.
  *   quats  device float [n_roi][4], in: start, out: refined
  *   a0     starting step (quaternion arc length, e.g. 0.01)
  *   score  device float [n_roi] or NULL, out: final J

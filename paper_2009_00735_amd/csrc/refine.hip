@@ -14,9 +14,7 @@
 // gfx950 design: one workgroup per (ROI, 256-direction tile); the ROI's
 // relative coordinates are staged in LDS (broadcast reads: every lane of a
 // wave reads the same atom), each lane owns one direction and all
-// frequencies (score and amplitudes, and the gradient of large calls, k_sf;
-// the gradient's sums of the others go to the matrix cores, k_sf_grad),
-// sin/cos by the hardware transcendental unit (v_sin_f32 and
+// frequencies, sin/cos by the hardware transcendental unit (v_sin_f32 and
 // v_cos_f32 take the phase in turns, so f * (u . x) needs no 2 pi and no
 // range reduction for |f u.x| < 256).  Per-tile partial sums (J and the
 // 3x3 G) are reduced across tiles in a fixed order by a second kernel, so
@@ -87,15 +85,6 @@ __device__ __forceinline__ void sf_direction(const float (&C)[NF], const float (
     }
 }
 
-// LDS operations of one wavefront complete in issue order; this keeps the
-// compiler from moving LDS accesses across the point.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int kRemAtoms = 16;   // a last tile with fewer directions runs atom-parallel
 
 __device__ __forceinline__ void swap_acc(float &a, float &b)
@@ -132,7 +121,7 @@ __device__ __forceinline__ void sf_term(const float4 x, float ax, float ay, floa
 }
 
 // MODE 0: score partials (the gradient slots zero); MODE 1: score and gradient
-// partials (the calls k_sf_grad does not take); MODE 2: amplitudes.
+// partials; MODE 2: amplitudes.
 // NF: number of frequencies (compile-time so the accumulators stay in VGPRs).
 // A last tile with fewer than kRemAtoms directions (e.g. the one direction
 // left after 20 full tiles of the 10242-node mesh's 5121 evaluated ones) is
@@ -285,280 +274,6 @@ __global__ __launch_bounds__(kTile) void k_sf(const float4 *__restrict__ rel, co
 #pragma unroll
         for (int w = 0; w < kTile / 64; ++w) x += threadIdx.x < kSums ? red[threadIdx.x][w] : 0.f;
         partials[((size_t)r * n_tiles + tile) * kPartial + threadIdx.x] = x;
-    }
-}
-
-// ------------------------------------------------- adjoint on matrix cores
-// The gradient's sums per direction and frequency, C, S (cos, sin) and
-// P, Q (x sin, x cos), are products of the matrix of sines (cosines), rows
-// directions and columns atoms, with the matrix [1 x y z] of the atoms.  The
-// sines are formed on the vector unit as before; the eight multiply-adds per
-// term become four v_mfma_f32_16x16x32_f16 per 16 directions, 32 atoms and
-// frequency, FP32 accumulation, with both factors split into two FP16 parts:
-// sin = h + l (22 bits), and columns [1, x_h, y_h, z_h, x_l, y_l, z_l] of the
-// scaled coordinates, so that (h + l) times every column is exact products.
-//
-// Bound: the vector unit.  Of about 170 cycles per atom and 64 directions at
-// four frequencies the eight sines and cosines take 70 (8.6 each, measured);
-// splitting a value takes 9.6 (two conversions for two values and a mixed
-// multiply-add) and its MFMAs 4, where its four FP32 multiply-adds took 11,
-// 128 ROIs of about 1200 atoms at 10242 directions and four
-// frequencies 1.00 ms, 1.12 ms with the FP32 multiply-adds.
-// Two groups of 16 directions per pass share the atoms' LDS reads (one group
-// measured 3-7 % slower at 1 to 4 frequencies, four 8 %, equal at 7 and 8).
-// v_fma_mixlo/mixhi_f16 for the low parts (three instructions per two values
-// instead of four) measured 6 % slower: they take 8.6 cycles each.
-//
-// Layout: a wavefront takes 16 G directions at a time; lane l forms the terms
-// of direction l % 16 of each of its G groups for atoms 8 (l / 16) .. + 7 of
-// the step, which is the A operand's layout.  The atoms sit in LDS as FP32
-// (read by 16 lanes at once) and as the FP16 column table (the B operand).
-// The D tiles pass through LDS once per group to the lane of (direction,
-// frequency).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kCols = 7;         // columns of the atom table
-constexpr int kStep = 32;        // atoms per MFMA
-constexpr int kRowF = 2 * kCols + 1;   // floats per (direction, frequency) in the exchange
-
-// 8 FP32 values of one row as FP16 parts; `minus` is -1, kept from the
-// compiler so that the remainder is one fused instruction.
-__device__ __forceinline__ void split8(const float (&x)[8], float minus, f16x8 &hi, f16x8 &lo)
-{
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(x[e], x[e + 1]));
-        hi[e] = h.x;
-        hi[e + 1] = h.y;
-        lo[e] = (_Float16)fmaf((float)h.x, minus, x[e]);
-        lo[e + 1] = (_Float16)fmaf((float)h.y, minus, x[e + 1]);
-    }
-}
-
-template <int NF, int G> struct SfStage {
-    float4 xs[kChunk];                                       // coordinates, zero past the end
-    _Float16 tab[kCols][kChunk + 32];                        // columns 1, hi, lo; rows 64 bytes apart in the banks
-    float ex[kTile / 64][16 * NF * kRowF];                   // D exchange, one region per wavefront
-    float red[kPartial][kTile / 64];
-};
-
-template <int NF, int G>
-__global__ __launch_bounds__(kTile) void k_sf_grad(const float4 *__restrict__ rel, const int64_t *__restrict__ offsets,
-                                                   const float *__restrict__ quats, const int32_t *__restrict__ phase,
-                                                   int n_phase, const float *__restrict__ dirs, int n_dir,
-                                                   const int32_t *__restrict__ rep, const int32_t *__restrict__ mate,
-                                                   const int32_t *__restrict__ n_eval_p, int n_tiles, int64_t n_roi,
-                                                   const float *__restrict__ freqs, const float *__restrict__ targets,
-                                                   float *__restrict__ partials, float *__restrict__ /* amplitudes: not this kernel's */)
-{
-    __shared__ SfStage<NF, G> st;
-    // XCD-aware order as in k_sf
-    const int64_t t = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (t >= n_roi * n_tiles) return;
-    const int64_t r = t / n_tiles;
-    const int tile = (int)(t - r * n_tiles);
-    const int n_eval = *n_eval_p;
-    if (tile * kTile >= n_eval) {
-        if (threadIdx.x < kPartial) partials[((size_t)r * n_tiles + tile) * kPartial + threadIdx.x] = 0.f;
-        return;
-    }
-    if (n_eval - tile * kTile < kRemAtoms) return;   // a short last tile: k_sf_rem writes it
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int row = lane & 15, part16 = lane >> 4;
-    const int p = min(max(phase[r], 0), n_phase - 1);   // out-of-range phases are clamped
-    float q[4] = {quats[4 * r], quats[4 * r + 1], quats[4 * r + 2], quats[4 * r + 3]};
-    float M[9];
-    rotation(q, M);
-    float f[NF];
-#pragma unroll
-    for (int w = 0; w < NF; ++w) f[w] = freqs[p * NF + w];
-    // slot 0 holds the frequency of largest |f| (index kb), as in k_sf
-    int kb = 0;
-#pragma unroll
-    for (int w = 1; w < NF; ++w)
-        if (fabsf(f[w]) > fabsf(f[kb])) kb = w;
-    const float fb = f[kb];
-    float g[NF];
-#pragma unroll
-    for (int w = 0; w < NF; ++w) {
-        const float fw = w == 0 ? fb : (w == kb ? f[0] : f[w]);
-        const float gw = fb != 0.f ? fw / fb : 0.f;
-        g[w] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gw)));
-    }
-    const int64_t off0 = offsets[r];
-    const int nw = (int)(offsets[r + 1] - off0);
-    // the coordinates' scale: a power of two that brings the largest below
-    // one, so that neither FP16 part overflows and the parts of the largest
-    // hold 22 bits
-    float big = 0.f;
-    for (int i = tid; i < nw; i += kTile) {
-        const float4 a = rel[off0 + i];
-        big = fmaxf(big, fmaxf(fabsf(a.x), fmaxf(fabsf(a.y), fabsf(a.z))));
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) big = fmaxf(big, __shfl_xor(big, o));
-    if (lane == 0) st.red[0][wave] = big;
-    __syncthreads();
-    big = fmaxf(fmaxf(st.red[0][0], st.red[0][1]), fmaxf(st.red[0][2], st.red[0][3]));
-    int ex = 0;
-    if (big > 0.f && big < INFINITY) (void)frexpf(big, &ex);   // big < 2^ex
-    ex = min(max(ex, -100), 100);
-    const float down = ldexpf(1.f, -ex), up = ldexpf(1.f, ex);
-    float minus = -1.0f;
-    asm("" : "+s"(minus));
-
-    float J = 0.f, part[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) part[k] = 0.f;
-    const int col = min(row, kCols - 1);              // columns past the table repeat its last and are not read
-    for (int pass = 0; pass < 4 / G; ++pass) {
-        const int d0 = tile * kTile + wave * 64 + pass * 16 * G;   // first evaluated direction of this pass
-        const bool busy = __builtin_amdgcn_readfirstlane(d0) < n_eval;
-        float ax[G], ay[G], az[G];
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int i = d0 + 16 * u + row;
-            const int v = i < n_eval ? rep[i] : 0;
-            const float nx = i < n_eval ? dirs[3 * v] : 0.f, ny = i < n_eval ? dirs[3 * v + 1] : 0.f,
-                        nz = i < n_eval ? dirs[3 * v + 2] : 0.f;
-            ax[u] = fb * (M[0] * nx + M[1] * ny + M[2] * nz);
-            ay[u] = fb * (M[3] * nx + M[4] * ny + M[5] * nz);
-            az[u] = fb * (M[6] * nx + M[7] * ny + M[8] * nz);
-        }
-        f32x4 sn[G][NF], cs[G][NF];
-#pragma unroll
-        for (int u = 0; u < G; ++u)
-#pragma unroll
-            for (int w = 0; w < NF; ++w) sn[u][w] = cs[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int c0 = 0; c0 < nw; c0 += kChunk) {
-            const int nc = min(kChunk, nw - c0);
-            const int np = (nc + kStep - 1) / kStep * kStep;
-            if (pass == 0 || nw > kChunk) {   // a ROI within one stage is staged once
-                __syncthreads();
-                for (int i = tid; i < np; i += kTile) {
-                    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (i < nc) a = rel[off0 + c0 + i];
-                    a.w = 0.f;
-                    st.xs[i] = a;
-                    const float x = a.x * down, y = a.y * down, z = a.z * down;
-                    const _Float16 hx = (_Float16)x, hy = (_Float16)y, hz = (_Float16)z;
-                    st.tab[0][i] = (_Float16)(i < nc ? 1.f : 0.f);
-                    st.tab[1][i] = hx;
-                    st.tab[2][i] = hy;
-                    st.tab[3][i] = hz;
-                    st.tab[4][i] = (_Float16)(x - (float)hx);
-                    st.tab[5][i] = (_Float16)(y - (float)hy);
-                    st.tab[6][i] = (_Float16)(z - (float)hz);
-                }
-                __syncthreads();
-            }
-            const int n_run = __builtin_amdgcn_readfirstlane(busy ? np : 0);
-#pragma unroll 1
-            for (int j = 0; j < n_run; j += kStep) {
-                const int k0 = j + 8 * part16;
-                const f16x8 b = *reinterpret_cast<const f16x8 *>(&st.tab[col][k0]);
-                float4 x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = st.xs[k0 + e];
-#pragma unroll
-                for (int u = 0; u < G; ++u) {
-                    float d[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) d[e] = fmaf(az[u], x[e].z, fmaf(ay[u], x[e].y, ax[u] * x[e].x));
-#pragma unroll
-                    for (int w = 0; w < NF; ++w) {
-                        float s8[8], c8[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float ph = w == 0 ? d[e] : g[w] * d[e];   // phase in turns
-                            s8[e] = __builtin_amdgcn_sinf(ph);
-                            c8[e] = __builtin_amdgcn_cosf(ph);
-                        }
-                        f16x8 hi, lo;
-                        split8(s8, minus, hi, lo);
-                        sn[u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, b, sn[u][w], 0, 0, 0);
-                        sn[u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, b, sn[u][w], 0, 0, 0);
-                        split8(c8, minus, hi, lo);
-                        cs[u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, b, cs[u][w], 0, 0, 0);
-                        cs[u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, b, cs[u][w], 0, 0, 0);
-                    }
-                }
-            }
-        }
-        // D layout: lane l, value i -> row 4 (l / 16) + i, column l % 16
-        const float inv_n = nw > 0 ? 1.0f / (float)nw : 0.f;
-        float *mine = st.ex[wave];
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int base = d0 + 16 * u;
-            if (__builtin_amdgcn_readfirstlane(base) >= n_eval) break;
-            wave_sync();
-            if (row < kCols) {
-#pragma unroll
-                for (int w = 0; w < NF; ++w)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float *o = mine + ((4 * part16 + i) * NF + w) * kRowF;
-                        o[row] = sn[u][w][i];
-                        o[kCols + row] = cs[u][w][i];
-                    }
-            }
-            wave_sync();
-            // lane: direction `row`, slots part16, part16 + 4
-            const int i_eval = base + row;
-            if (i_eval < n_eval) {
-                const int v = rep[i_eval], vm = mate[i_eval];
-                const float nx = dirs[3 * v], ny = dirs[3 * v + 1], nz = dirs[3 * v + 2];
-                float gu[3] = {0.f, 0.f, 0.f};
-                for (int w = part16; w < NF; w += 4) {
-                    const float *o = mine + (row * NF + w) * kRowF;
-                    const int wf = w == 0 ? kb : (w == kb ? 0 : w);   // the slot's frequency
-                    float fw = 0.f;
-#pragma unroll
-                    for (int c = 0; c < NF; ++c)
-                        if (c == wf) fw = f[c];
-                    const float S = o[0], C = o[kCols];
-                    const float mag = sqrtf(fmaf(C, C, S * S));
-                    const float A = mag * inv_n;
-                    const float e = A - targets[((size_t)p * NF + wf) * n_dir + v];
-                    const float em = vm >= 0 ? A - targets[((size_t)p * NF + wf) * n_dir + vm] : 0.f;
-                    J = fmaf(e, e, J);
-                    J = fmaf(em, em, J);
-                    if (mag >= 1e-12f * (float)nw && nw > 0) {
-                        const float k = 2.0f * (e + em) * inv_n * 6.283185307179586f * fw / mag;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            const float P = up * (o[1 + c] + o[4 + c]), Q = up * (o[kCols + 1 + c] + o[kCols + 4 + c]);
-                            gu[c] = fmaf(k, S * Q - C * P, gu[c]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    part[3 * c] = fmaf(gu[c], nx, part[3 * c]);
-                    part[3 * c + 1] = fmaf(gu[c], ny, part[3 * c + 1]);
-                    part[3 * c + 2] = fmaf(gu[c], nz, part[3 * c + 2]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kPartial; ++k) {
-        float x = k == 0 ? J : part[k > 0 ? k - 1 : 0];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        if (k == 0) __syncthreads();   // every wave has read the scale from red
-        if (lane == 0) st.red[k][wave] = x;
-    }
-    __syncthreads();
-    if (tid < kPartial) {
-        float x = 0.f;
-#pragma unroll
-        for (int w = 0; w < kTile / 64; ++w) x += st.red[tid][w];
-        partials[((size_t)r * n_tiles + tile) * kPartial + tid] = x;
     }
 }
 
@@ -1005,33 +720,6 @@ template <int MODE> SfFn sf_kernel(int n_freq)
     }
 }
 
-// The gradient's kernel for n_roi * n_tiles workgroups.  At one and four
-// frequencies k_sf<1,NF> forms the sums faster once every CU has several
-// workgroups after another: k_sf_grad's exchange of the sums costs a tile of
-// few atoms more, and its instruction mix no longer fills the gaps of a last
-// round.  us per evaluation (vector / matrix form) at 10242 directions and
-// four frequencies, 128, 256, 512 and 1000 ROIs: of 2000 atoms 1094 / 998,
-// 1904 / 1852, 3540 / 3574, 6612 / 6812; of 250 atoms 190 / 188, 302 / 324,
-// 526 / 604, 944 / 1126.  The line lies at 300 ROIs.  Two, three, six and
-// eight frequencies stay with k_sf_grad (600 ROIs of 850 atoms, 7, 4, 4 and
-// 6 % faster; one frequency 6 % slower).
-constexpr int64_t kVectorTiles = 12288;
-bool sf_vector_form(int n_freq, int64_t tiles) { return tiles >= kVectorTiles && (n_freq == 1 || n_freq == 4); }
-SfFn sf_grad_kernel(int n_freq, int64_t tiles)
-{
-    if (sf_vector_form(n_freq, tiles)) return n_freq == 1 ? sf::k_sf<1, 1> : sf::k_sf<1, 4>;
-    switch (n_freq) {
-    case 1: return sf::k_sf_grad<1, 2>;
-    case 2: return sf::k_sf_grad<2, 2>;
-    case 3: return sf::k_sf_grad<3, 2>;
-    case 4: return sf::k_sf_grad<4, 2>;
-    case 5: return sf::k_sf_grad<5, 2>;
-    case 6: return sf::k_sf_grad<6, 2>;
-    case 7: return sf::k_sf_grad<7, 1>;
-    default: return sf::k_sf_grad<8, 1>;
-    }
-}
-
 template <int MODE> SfRemFn sf_rem_kernel(int n_freq)
 {
     switch (n_freq) {
@@ -1058,7 +746,7 @@ static ar_status sf_launch_ws(int mode, const float *rel, const int64_t *offsets
     const int32_t *rep = list + n_dir, *mate = list + 2 * n_dir, *n_eval = list + 3 * n_dir;
     const int n_tiles = (n_dir + sf::kTile - 1) / sf::kTile;
     const SfFn fn = mode == 2   ? sf_kernel<2>(n_freq)
-                    : mode == 1 ? sf_grad_kernel(n_freq, n_roi * n_tiles)
+                    : mode == 1 ? sf_kernel<1>(n_freq)
                                 : sf_kernel<0>(n_freq);
     const SfRemFn fr = mode == 2   ? sf_rem_kernel<2>(n_freq)
                        : mode == 1 ? sf_rem_kernel<1>(n_freq)
@@ -1223,14 +911,12 @@ ar_status ar_refine_orientations(ar_context *ctx, const float *rel, const int64_
     ar::sf::k_copy4<<<(unsigned)((4 * n_roi + 255) / 256), 256, 0, s>>>(quats, trial, n_roi);
     AR_HIP(hipGetLastError());
     AR_TRY(ar::eval_list(ctx, directions, n_dir, s));
-    // The last evaluation only decides whether its trial is accepted: score
-    // alone (the forward kernel, about half the adjoint's work), where that
-    // forms the same sums as the evaluations it is compared with.
-    const int64_t tiles = n_roi * ((n_dir + ar::sf::kTile - 1) / ar::sf::kTile);
-    const int last_mode = steps == 0 || ar::sf_vector_form(n_freq, tiles) ? 0 : 1;
     for (int it = 0; it <= steps; ++it) {
+        // the last evaluation only decides whether its trial is accepted:
+        // score alone (the forward kernel, about half the adjoint's work; the
+        // same sums, so the same J)
         const bool last = it == steps;
-        AR_TRY(ar::sf_launch(ctx, last ? last_mode : 1, rel, offsets, n_roi, trial, phase, n_phase, directions, n_dir, freqs, targets,
+        AR_TRY(ar::sf_launch(ctx, last ? 0 : 1, rel, offsets, n_roi, trial, phase, n_phase, directions, n_dir, freqs, targets,
                              n_freq, Jt, gt, nullptr, s, true));
         ar::sf::k_refine_update<<<nb, 256, 0, s>>>(st, trial, Jt, last ? nullptr : gt, n_roi, it == 0 ? 1 : 0, a0);
         AR_HIP(hipGetLastError());

@@ -23,9 +23,8 @@ class SFScore(torch.autograd.Function):
     (256 ROIs, 10242 directions, 4 frequencies: 2.11 ms against 3.65).  A
     forward pass whose gradient is never taken costs 1.4 times the score
     alone; under no_grad, or for quaternions that need no gradient, only the
-    score is formed (the two may differ in their last bits, about 1e-7 of J:
-    compare scores formed in one way).  The inputs are saved as well: a change in place between
-    the passes is an error."""
+    score is formed, with the same value.  The inputs are saved as well: a
+    change in place between the passes is an error."""
 
     @staticmethod
     def forward(ctx, quats, actx, rel, offsets, phase, directions, freqs, targets, want_grad=None):
