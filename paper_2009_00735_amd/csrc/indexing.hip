@@ -632,10 +632,19 @@ __global__ __launch_bounds__(256) void k_merge64(const float *__restrict__ in_s,
 // ------------------------------------------------------------ FP32 rescore
 // One workgroup per ROI row: Delta for each candidate from the FP32 images,
 // then the k best by (Delta, index).  Bound: the candidates' rows from memory.
-// Sixteen wavefronts, one candidate each of 16: a call of 16 ROIs and 642
-// directions takes 37 us, with four wavefronts 45; 20000 ROIs and 10242
-// directions 148.4 ms, 149.2.
-constexpr int kRescoreWaves = 16;
+// WAVES: sixteen wavefronts, one candidate each of 16, shorten a ROI's time,
+// which is what a call waits for while its ROIs are resident together (two
+// workgroups of 1024 threads per CU); past that they pay where the rows are
+// long, and with 64 candidates.  us per call with 4 / 16 wavefronts and 600
+// references, 16 candidates of 4 windows: 512 ROIs of 642 directions 54 / 43,
+// 8192 of 642 296 / 341, 100000 of 42 1038 / 1655, 2048 of 10242 980 / 893; 32
+// candidates, 2048 ROIs of 2562 321 / 339, of 10242 1521 / 1468, 8192 of one
+// window of 10242 1482 / 1515; 64 candidates, 8192 of 642 1234 / 1015.
+inline bool wide_rescore(int cand, int64_t n_roi, int n_win, int n_dir, int cus)
+{
+    return n_roi <= 2 * cus || cand == 64 ||
+           (n_dir >= 8192 && (cand == 16 || (int64_t)n_win * n_dir >= 32768));
+}
 template <int CAND, bool STAGE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_rescore(const float *__restrict__ S, const float *__restrict__ inv_s,
                                                  const float *__restrict__ L, const float *__restrict__ inv_l,
@@ -712,9 +721,10 @@ ar_status launch_rescore(ar_context *ctx, const float *images, const ar_library 
                          int32_t *top_idx, float *top_score, hipStream_t s)
 {
     const size_t stage = sizeof(float) * (size_t)lib->n_dir;
-    constexpr int W = kRescoreWaves;
+    const int W = wide_rescore(CAND, n_roi, lib->n_win, lib->n_dir, ctx->cu_count) ? 16 : 4;
     const bool staged = stage + 4096 <= (size_t)ctx->lds_per_block;
-    const auto fn = staged ? k_rescore<CAND, true, W> : k_rescore<CAND, false, W>;
+    const auto fn = W == 16 ? (staged ? k_rescore<CAND, true, 16> : k_rescore<CAND, false, 16>)
+                            : (staged ? k_rescore<CAND, true, 4> : k_rescore<CAND, false, 4>);
     if (staged && stage > 65536)   // on every launch: the attribute belongs to the current device
         AR_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)stage));
     return by_rows(n_roi, 64 * W, [&](int64_t r0, unsigned n) {

@@ -823,11 +823,16 @@ __global__ __launch_bounds__(256) void k_sparse_merge(const float *__restrict__ 
 // (n_dir floats), so the per-entry gathers read LDS; otherwise they read the
 // image in global memory.  Either way d = x * (1 / max) - R_i as in the
 // screens' normalisation, the square accumulated with one FMA.
-// Sixteen wavefronts, one candidate each of 16: 2000 ROIs, 1000 entries 98 us,
-// with four wavefronts 154.
-constexpr int kRescoreWaves = 16;
-template <int CAND, bool STAGE>
-__global__ __launch_bounds__(64 * kRescoreWaves) void k_sparse_rescore(
+// WAVES: sixteen wavefronts, one candidate each of 16 (2000 ROIs, 1000 entries
+// 98 us, with four wavefronts 154); four for many ROIs of few entries, where the
+// workgroups' start counts more (8192 ROIs, 100 entries, 642 directions, the
+// whole call 592 us, with sixteen 605; 2048 ROIs 162 with either).
+inline bool wide_rescore(int cand, int64_t n_roi, int n_hat, int n_dir, int cus)
+{
+    return cand != 16 || n_roi <= 8 * cus || n_hat > 256 || n_dir >= 8192;
+}
+template <int CAND, bool STAGE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_sparse_rescore(
     const float *__restrict__ S, const float *__restrict__ inv_s, int n_win, int n_dir,
     const int32_t *__restrict__ cseg, const float *__restrict__ sval_w, const uint16_t *__restrict__ lut_gi,
     int n_hat, const int64_t *__restrict__ phase_start, int n_phase, int64_t n_lib,
@@ -837,7 +842,7 @@ __global__ __launch_bounds__(64 * kRescoreWaves) void k_sparse_rescore(
     extern __shared__ float stage[];
     __shared__ float ds[CAND];
     __shared__ int di[CAND];
-    constexpr int WAVES = kRescoreWaves, PER = CAND / WAVES;   // candidates per wave
+    constexpr int PER = CAND / WAVES;   // candidates per wave
     constexpr int THREADS = 64 * WAVES, AHEAD = 64 / WAVES;
     const int64_t r = blockIdx.x;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -934,10 +939,12 @@ ar_status merge_rescore(ar_context *ctx, const ar_sparse_lut *lut, const float *
     // stage each ROI window in LDS when n_dir floats fit beside the static arrays
     const size_t stage = sizeof(float) * (size_t)lut->n_dir;
     const bool staged = stage + 4096 <= (size_t)ctx->lds_per_block;
-    const auto fn = staged ? k_sparse_rescore<CAND, true> : k_sparse_rescore<CAND, false>;
+    const int W = wide_rescore(CAND, n_roi, lut->n_hat, lut->n_dir, ctx->cu_count) ? 16 : 4;
+    const auto fn = W == 16 ? (staged ? k_sparse_rescore<CAND, true, 16> : k_sparse_rescore<CAND, false, 16>)
+                            : (staged ? k_sparse_rescore<CAND, true, 4> : k_sparse_rescore<CAND, false, 4>);
     if (staged) AR_TRY(allow_lds(fn, stage));
-    return by_rows(n_roi, 64 * kRescoreWaves, [&](int64_t r0, unsigned n) {
-        fn<<<n, 64 * kRescoreWaves, staged ? stage : 0, s>>>(
+    return by_rows(n_roi, 64 * W, [&](int64_t r0, unsigned n) {
+        fn<<<n, 64 * W, staged ? stage : 0, s>>>(
             images + (size_t)r0 * lut->n_win * lut->n_dir, ctx->sp_inv.as<float>() + r0 * lut->n_win, lut->n_win,
             lut->n_dir, lut->cseg.as<int32_t>(), lut->sval_w.as<float>(), lut->lut_gi.as<uint16_t>(), lut->n_hat,
             lut->phase_start.as<int64_t>(), lut->n_phase, lut->n_lib, ctx->sp_merge.as<int32_t>() + r0 * CAND, k,
