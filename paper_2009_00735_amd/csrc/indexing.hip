@@ -54,10 +54,13 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_floa
 // grid (rows with padding, n_win); writes inv_max[row][w] and
 // out[row][w*n_dir + v] of the n rows, zeros in the rows past them.  The
 // workgroup of the last window also zeroes the K padding of its row.
-// Bound: memory.  A window of up to 512 kKeep directions stays in registers
+// Bound: memory.  A window of up to 512 KEEP directions stays in registers
 // between its maximum and its copy; read twice, 2000 x 10242 directions took
-// 160 us, now 85.
-constexpr int kKeep = 20;   // pairs per thread: 10240 directions and the two of a geodesic mesh's poles
+// 160 us, now 85.  KEEP is 20 (10240 directions and the two of a geodesic mesh's
+// poles) or, for up to 1024 directions, 2: the pairs a thread does not have cost
+// it instructions all the same (100000 ROIs of 4 x 12 directions and 10
+// references, the whole call: 1205 us with 20, 930 with 2).
+template <int KEEP>
 __global__ __launch_bounds__(256) void k_normalise_cast(const float *__restrict__ img, int64_t n, int n_win, int n_dir,
                                                         int64_t Kp, float *__restrict__ inv_max,
                                                         uint16_t *__restrict__ out)
@@ -82,16 +85,16 @@ __global__ __launch_bounds__(256) void k_normalise_cast(const float *__restrict_
     const bool pairs = (n_dir & 1) == 0 && (reinterpret_cast<uintptr_t>(img) & 7) == 0;
     const float2 *s2 = reinterpret_cast<const float2 *>(src);
     const int half = n_dir / 2;
-    float2 x[kKeep];
+    float2 x[KEEP];
     float m = 0.0f;
     if (pairs) {
 #pragma unroll
-        for (int j = 0; j < kKeep; ++j)
+        for (int j = 0; j < KEEP; ++j)
             if (j * 256 + tid < half) x[j] = s2[j * 256 + tid];
 #pragma unroll
-        for (int j = 0; j < kKeep; ++j)
+        for (int j = 0; j < KEEP; ++j)
             if (j * 256 + tid < half) m = fmaxf(m, fmaxf(x[j].x, x[j].y));
-        for (int v = kKeep * 256 + tid; v < half; v += 256) m = fmaxf(m, fmaxf(s2[v].x, s2[v].y));
+        for (int v = KEEP * 256 + tid; v < half; v += 256) m = fmaxf(m, fmaxf(s2[v].x, s2[v].y));
     } else {
         for (int v = tid; v < n_dir; v += 256) m = fmaxf(m, src[v]);
     }
@@ -108,9 +111,9 @@ __global__ __launch_bounds__(256) void k_normalise_cast(const float *__restrict_
             d2[v] = (uint32_t)f32_to_bf16_rne(y.x * inv) | ((uint32_t)f32_to_bf16_rne(y.y * inv) << 16);
         };
 #pragma unroll
-        for (int j = 0; j < kKeep; ++j)
+        for (int j = 0; j < KEEP; ++j)
             if (j * 256 + tid < half) put(j * 256 + tid, x[j]);
-        for (int v = kKeep * 256 + tid; v < half; v += 256) put(v, s2[v]);
+        for (int v = KEEP * 256 + tid; v < half; v += 256) put(v, s2[v]);
     } else {
         for (int v = tid; v < n_dir; v += 256) dst[v] = f32_to_bf16_rne(src[v] * inv);
     }
@@ -841,8 +844,9 @@ int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 ar_status normalise_cast(const float *img, int64_t n, int64_t n_pad, int n_win, int n_dir, int64_t Kp, float *inv,
                          uint16_t *out, hipStream_t s)
 {
+    const auto fn = n_dir <= 1024 ? k_normalise_cast<2> : k_normalise_cast<20>;
     return by_rows(n_pad, 256, [&](int64_t r0, unsigned rows) {
-        k_normalise_cast<<<dim3(rows, (unsigned)n_win), 256, 0, s>>>(img + (size_t)r0 * n_win * n_dir, n - r0, n_win, n_dir,
+        fn<<<dim3(rows, (unsigned)n_win), 256, 0, s>>>(img + (size_t)r0 * n_win * n_dir, n - r0, n_win, n_dir,
                                                                      Kp, inv + r0 * n_win, out + (size_t)r0 * Kp);
     });
 }

@@ -447,15 +447,18 @@ __global__ __launch_bounds__(256) void k_sparse_norm(const float *__restrict__ i
 // grid (n_grp, n_win), 8 ROIs per group.  q8[grp][w][slab bytes]: byte
 // v * 8 + j = round(255 s) of ROI grp * 8 + j at node v, s the normalised value
 // (clamped to [0, 1]); node n_dir, ROIs past n_roi and padding are zero.
-// Bound: memory.  The first kNormKeep nodes of every thread stay in registers
+// Bound: memory.  The first KEEP nodes of every thread stay in registers
 // between the eight maxima and the codes (2000 ROIs x 10242 directions
-// 81 us; read twice 207).
-constexpr int kNormThreads = 1024, kNormKeep = 10;
-__global__ __launch_bounds__(kNormThreads) void k_sparse_norm8(const float *__restrict__ img, int64_t n_roi, int n_win,
+// 81 us; read twice 207).  1024 threads keep 10, or 256 threads 3 where those
+// are the whole window: threads and nodes that are not there cost
+// instructions all the same (2000 ROIs of 162 directions, the whole call: 98
+// us, now 80).
+template <int THREADS, int KEEP>
+__global__ __launch_bounds__(THREADS) void k_sparse_norm8(const float *__restrict__ img, int64_t n_roi, int n_win,
                                                                int n_dir, int64_t slab, float *__restrict__ inv_s,
                                                                uint32_t *__restrict__ q8)
 {
-    __shared__ float part[kNormThreads / 64][8];
+    __shared__ float part[THREADS / 64][8];
     __shared__ float inv[8];
     const int64_t grp = blockIdx.x;
     const int w = blockIdx.y;
@@ -463,21 +466,21 @@ __global__ __launch_bounds__(kNormThreads) void k_sparse_norm8(const float *__re
     const int nr = (int)min((int64_t)8, n_roi - grp * 8);
     const float *src = img + ((size_t)grp * 8 * n_win + w) * n_dir;   // ROI j at src + j * n_win * n_dir
     const size_t rs = (size_t)n_win * n_dir;
-    float x[kNormKeep][8], m[8];
+    float x[KEEP][8], m[8];
 #pragma unroll
-    for (int e = 0; e < kNormKeep; ++e)
+    for (int e = 0; e < KEEP; ++e)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int v = tid + kNormThreads * e;
+            const int v = tid + THREADS * e;
             x[e][j] = j < nr && v < n_dir ? src[j * rs + v] : 0.0f;
         }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         m[j] = 0.0f;
 #pragma unroll
-        for (int e = 0; e < kNormKeep; ++e) m[j] = fmaxf(m[j], x[e][j]);
+        for (int e = 0; e < KEEP; ++e) m[j] = fmaxf(m[j], x[e][j]);
         if (j < nr)
-            for (int v = tid + kNormThreads * kNormKeep; v < n_dir; v += kNormThreads) m[j] = fmaxf(m[j], src[j * rs + v]);
+            for (int v = tid + THREADS * KEEP; v < n_dir; v += THREADS) m[j] = fmaxf(m[j], src[j * rs + v]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) m[j] = fmaxf(m[j], __shfl_xor(m[j], off));
         if (lane == 0) part[wave][j] = m[j];
@@ -486,7 +489,7 @@ __global__ __launch_bounds__(kNormThreads) void k_sparse_norm8(const float *__re
     if (tid < 8) {
         float mx = part[0][tid];
 #pragma unroll
-        for (int u = 1; u < kNormThreads / 64; ++u) mx = fmaxf(mx, part[u][tid]);
+        for (int u = 1; u < THREADS / 64; ++u) mx = fmaxf(mx, part[u][tid]);
         inv[tid] = mx > 0.0f ? 1.0f / mx : 0.0f;
         if (tid < nr) inv_s[(size_t)(grp * 8 + tid) * n_win + w] = inv[tid];
     }
@@ -502,9 +505,9 @@ __global__ __launch_bounds__(kNormThreads) void k_sparse_norm8(const float *__re
         dst[v] = make_uint2(word[0], word[1]);
     };
 #pragma unroll
-    for (int e = 0; e < kNormKeep; ++e)
-        if (tid + kNormThreads * e < n_nodes) put(tid + kNormThreads * e, x[e]);
-    for (int v = tid + kNormThreads * kNormKeep; v < n_nodes; v += kNormThreads) {
+    for (int e = 0; e < KEEP; ++e)
+        if (tid + THREADS * e < n_nodes) put(tid + THREADS * e, x[e]);
+    for (int v = tid + THREADS * KEEP; v < n_nodes; v += THREADS) {
         float y[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) y[j] = j < nr && v < n_dir ? src[j * rs + v] : 0.0f;
@@ -1006,7 +1009,9 @@ ar_status run_screen8(ar_context *ctx, const ar_sparse_lut *lut, const float *im
     AR_CHECK((size_t)ctx->lds_per_block >= p.lds, "sparse screen needs %zu bytes of LDS", p.lds);
     AR_TRY(ctx->sp_cand_s.reserve(sizeof(float) * (size_t)(p.n_grp * 8 * lut->n_chunks * 2 * CAND)));
     AR_TRY(ctx->sp_cand_i.reserve(sizeof(int32_t) * (size_t)(p.n_grp * 8 * lut->n_chunks * 2 * CAND)));
-    k_sparse_norm8<<<dim3((unsigned)p.n_grp, (unsigned)lut->n_win), kNormThreads, 0, s>>>(
+    const int threads = p.slab <= 8 * 256 * 3 ? 256 : 1024;
+    const auto norm = threads == 256 ? k_sparse_norm8<256, 3> : k_sparse_norm8<1024, 10>;
+    norm<<<dim3((unsigned)p.n_grp, (unsigned)lut->n_win), threads, 0, s>>>(
         images, n_roi, lut->n_win, lut->n_dir, p.slab, ctx->sp_inv.as<float>(), ctx->sp_half.as<uint32_t>());
     AR_HIP(hipGetLastError());
     AR_TRY(allow_lds(k_sparse_screen8<CAND>, p.lds));
