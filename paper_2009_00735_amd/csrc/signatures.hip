@@ -1060,6 +1060,9 @@ ar_status ar_signature_plan_run(ar_plan *p, const float *rel, const int64_t *off
             AR_HIP(hipGraphDestroy(p->graph));
             p->graph = nullptr;
         }
+        // the twiddle table's first use copies it to the device, which a capture refuses
+        const float2 *W = nullptr;
+        AR_TRY(p->ctx->twiddle_table(p->nbins, &W));
         // capture on a private stream so the caller's stream may be the null stream
         hipStream_t cs;
         AR_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
