@@ -246,43 +246,10 @@ def main():
         "transcendentals_per_s": 2.0 * achieved_terms,
         "frac_of_measured_sin": 2.0 * achieved_terms / peaks["sin_per_s"],
     }
-    # signatures (a2-a5), unit = one ROI x direction, against the measured
-    # peaks of the three units the kernel uses:
-    #   FP32 flops: 7 N_w (Eq. (1)) + 2.5 N_b log2 N_b (real FFT, the paper's
-    #     cost model).  The kernel forms the last FFT stage only for the window
-    #     bins, so it executes fewer: 7 N_w + 5 N_c log2 NS + per window bin
-    #     two (R-1)-term complex sums (8 flops each) + 20 for |X_k|;
-    #   LDS atomics: N_w;
-    #   LDS bytes: 12 N_w atom reads, 4 N_b zeroing, 4 N_b histogram read,
-    #     (2P - 1) 4 N_b for the P passes before the last stage (writes and
-    #     reads of N_b/2 complex), 16 R per window bin for the last stage.
-    # frac = max over the units of achieved rate / measured peak.
+    # signatures (a2-a5), unit = one ROI x direction
     sig_s = stage_ms["a2_a5"] / 1e3
-    units = float(n_roi * n_dir)
-    nc = nb // 2
-    ns_last = 1
-    while nc // ns_last > 8:
-        ns_last *= 8
-    r_last = nc // ns_last
-    passes = int(round(math.log(ns_last, 8)))
-    n_bins_win = int(windows[:, 1].max() - windows[:, 0].min() + 1)
-    flop_full = 7.0 * n_w_mean + 2.5 * nb * math.log2(nb)
-    flop_pruned = 7.0 * n_w_mean + 5.0 * nc * math.log2(ns_last) + n_bins_win * (16.0 * (r_last - 1) + 20.0)
-    lds_bytes = 12.0 * n_w_mean + 8.0 * nb + (2 * passes - 1) * 4.0 * nb + 16.0 * r_last * n_bins_win
-    fr = {
-        "fp32_flops_full_fft": flop_full * units / sig_s / peaks["fp32_fma_flop_per_s"],
-        "fp32_flops_executed": flop_pruned * units / sig_s / peaks["fp32_fma_flop_per_s"],
-        "lds_atomics": n_w_mean * units / sig_s / peaks["lds_atomics_per_s"],
-        "lds_bytes": lds_bytes * units / sig_s / peaks["lds_bytes_per_s"],
-    }
-    bound = max(fr, key=fr.get)
-    roof_sig = {"kernel": "k_signatures_persistent<10,*> (a2-a5)", "bound": bound, "frac": fr[bound],
-                "frac_by_unit": fr, "peaks": "measured (ar_measure_peaks)",
-                "per_roi_direction": {"flop_full_fft": flop_full, "flop_executed": flop_pruned,
-                                      "lds_atomics": n_w_mean, "lds_bytes": lds_bytes},
-                "achieved_tflops_full_fft": flop_full * units / sig_s / 1e12,
-                "frac_of_published_fp32": flop_full * units / sig_s / PEAK_FP32_VECTOR,
-                "hbm_gbps": (16.0 * counts.sum() + 4.0 * n_roi * n_win * n_dir) / sig_s / 1e9}
+    roof_sig = signature_roofline(n_w_mean, nb, float(n_roi * n_dir), sig_s, peaks)
+    roof_sig["hbm_gbps"] = (16.0 * counts.sum() + 4.0 * n_roi * n_win * n_dir) / sig_s / 1e9
     Kp = lib.n_win * lib.n_dir
     Kp = (Kp + 63) // 64 * 64
     gemm_flops = 2.0 * ((n_roi + 127) // 128 * 128) * ((n_lib + 127) // 128 * 128) * Kp
@@ -357,10 +324,35 @@ def sf_flop_per_term(n_freq: int, adjoint: bool) -> float:
     return 1.0 + 2.0 + 5.0 / n_freq + (12.0 if adjoint else 0.0)
 
 
-def signature_flops(n_w: float, nb: int) -> float:
-    """FP32 flops per ROI x direction in the paper's cost model: 7 N_w for
-    Eq. (1) and 2.5 N_b log2 N_b for the real FFT."""
-    return 7.0 * n_w + 2.5 * nb * math.log2(nb)
+def signature_work(n_w: float, nb: int) -> dict:
+    """What the windowed signatures (k_signatures_*_mm: windows within 32 bins,
+    up to 2048 bins) do per ROI x direction, by unit.  D = 4096 / N_b directions
+    share an atom's read and two share a histogram word; N_2 = N_b / 64.
+      FP32 flops: 7 N_w (Eq. (1)), 8 per term of the outer sums (N_2 of them for
+        each of 32 bins) and 4 per amplitude;
+      FP16 matrix flops: cosine and sine products of 32 pairs, N_2 rows and 32
+        columns, the tables in two parts;
+      LDS atomics: N_w;
+      LDS bytes: 12 N_w / D of atoms, 2 N_b each to clear and to read the
+        histogram, 8 per amplitude.
+    paper_flops is the paper's cost model, 7 N_w + 2.5 N_b log2 N_b; no FFT is run."""
+    n2, d = nb // 64, 4096 // nb
+    return {"fp32_flops": 7.0 * n_w + 8.0 * 32 * n2 + 4.0 * 32, "fp16_mfma_flops": 4 * n2 * 32.0 * 32 * 2,
+            "lds_atomics": n_w, "lds_bytes": 12.0 * n_w / d + 4.0 * nb + 8.0 * 32,
+            "paper_flops": 7.0 * n_w + 2.5 * nb * math.log2(nb)}
+
+
+def signature_roofline(n_w: float, nb: int, units: float, seconds: float, peaks: dict) -> dict:
+    """signature_work against the measured peaks; frac is the largest unit's."""
+    work = signature_work(n_w, nb)
+    peak = {"fp32_flops": peaks["fp32_fma_flop_per_s"], "fp16_mfma_flops": peaks["bf16_mfma_flop_per_s"],
+            "lds_atomics": peaks["lds_atomics_per_s"], "lds_bytes": peaks["lds_bytes_per_s"]}
+    fr = {k: work[k] * units / seconds / p for k, p in peak.items()}
+    bound = max(fr, key=fr.get)
+    return {"kernel": f"k_signatures_persistent_mm<{nb.bit_length() - 1}> (a2-a5)", "bound": bound, "frac": fr[bound],
+            "frac_by_unit": fr, "peaks": "measured (ar_measure_peaks); the FP16 products against the BF16 rate",
+            "per_roi_direction": work, "achieved": work[bound] * units / seconds, "peak": peak[bound],
+            "paper_cost_model_tflops": work["paper_flops"] * units / seconds / 1e12}
 
 
 def event_ms(torch, fn, reps: int):
@@ -414,7 +406,6 @@ def config_legs(nat, synth, torch, dev, ctx, peaks, args):
     ms = event_ms(torch, lambda: plan.run(rel3, off3, R, dirs, w, out=img3, use_graph=True), reps)
     counts3 = torch.diff(off3).cpu().numpy()
     units = len(s3.centres) * n_dir
-    flop = signature_flops(float(counts3.mean()), NB)
     t0 = time.perf_counter()
     sel = np.linspace(0, len(s3.centres) - 1, 4).astype(int)
     orc.signatures(s3.positions, s3.centres[sel], R, s3.directions, NB, w.numpy(), threads)
@@ -425,11 +416,7 @@ def config_legs(nat, synth, torch, dev, ctx, peaks, args):
         "value": units / (ms / 1e3), "unit": "ROI·direction/s", "ms": ms,
         "atoms_min": int(counts3.min()), "atoms_max": int(counts3.max()), "atoms_mean": float(counts3.mean()),
         "plan": dict(zip(["dirs_per_item", "atoms_per_stage", "blocks_per_cu", "min_waves"], plan.config())),
-        "roofline": {"bound": "fp32_flops_full_fft", "achieved": flop * units / (ms / 1e3) / 1e12,
-                     "peak": PEAK_FP32_VECTOR / 1e12, "unit": "TFLOP/s",
-                     "frac": flop * units / (ms / 1e3) / PEAK_FP32_VECTOR,
-                     "frac_of_measured_fp32_fma": flop * units / (ms / 1e3) / peaks["fp32_fma_flop_per_s"],
-                     "flop_per_roi_direction": flop},
+        "roofline": signature_roofline(float(counts3.mean()), NB, float(units), ms / 1e3, peaks),
         "cpu_baseline": {"value": len(sel) * n_dir / t_o, "unit": "ROI·direction/s", "cores": threads,
                          "kind": "oracle", "sample": f"{len(sel)} of 8000 ROIs, all 10242 directions, {t_o:.1f} s"}}
     del plan, img3, rel3, off3
@@ -734,23 +721,24 @@ def compare(nat, synth, torch, dev):
     log("compare: typed signatures done")
     # reciprocal-space signatures on a cubic grid (Eq. (2)): the paper's
     # benchmark shape, 10^4 ROIs of R = 2 nm in full-density fcc Al, L = 64
-    # (and fewer of them at L = 128, 256, 512); algorithmic work 8 N_w L^3 flop per ROI
-    # (one complex multiply-add per atom and grid point)
+    # (and fewer of them at L = 128, 256, 512).  Work run: eight real sums per
+    # point of an octant, three FP16 products each, 6 N_w L^3 flop per ROI; a
+    # complex multiply-add per atom and grid point would be 8 N_w L^3
     del pos_d, types_d, cen_d
     pos, cen, _ = synth.fsp_specimen(10000, 2.0)
     off, rel = nat.ar_roi_gather(ctx, torch.from_numpy(pos).to(dev), torch.from_numpy(cen).to(dev), 2.0)
     rel = rel.contiguous()
     n_atoms = int(off[-1])
     fsp = {"rois": len(cen), "mean_atoms": n_atoms / len(cen), "k_max_per_nm": 10.0,
-           "measured_fp32_mfma_flop_per_s": peaks["fp32_mfma_flop_per_s"]}
+           "measured_mfma_flop_per_s": peaks["bf16_mfma_flop_per_s"]}
     for L, n in ((64, len(cen)), (128, 2000), (256, 200), (512, 24)):
         o = off[:n + 1]
         out = torch.empty((n, L, L, L), dtype=torch.float32, device=dev)
         t = best_ms(lambda: nat.ar_fsp_amplitudes(ctx, rel, o, L, 10.0, out=out))
-        flops = 8.0 * float(o[-1]) * L ** 3
-        fsp[f"L{L}"] = {"rois": n, "ms": t, "tflop_per_s": flops / (t / 1e3) / 1e12,
-                        "frac_of_datasheet_fp32_mfma": flops / (t / 1e3) / 157.3e12,
-                        "frac_of_measured_fp32_mfma": flops / (t / 1e3) / peaks["fp32_mfma_flop_per_s"],
+        flops = 6.0 * float(o[-1]) * L ** 3
+        fsp[f"L{L}"] = {"rois": n, "ms": t, "fp16_tflop_per_s": flops / (t / 1e3) / 1e12,
+                        "frac_of_measured_mfma": flops / (t / 1e3) / peaks["bf16_mfma_flop_per_s"],
+                        "complex_gemm_tflop_per_s": flops * 8 / 6 / (t / 1e3) / 1e12,
                         "output_gb": n * L ** 3 * 4 / 1e9}
         del out
     x0 = orc.roi_gather(pos, cen[0], 2.0)
