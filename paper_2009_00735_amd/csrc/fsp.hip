@@ -35,13 +35,15 @@
 // cycles per 16 atoms.  The factors are double buffered and the two
 // wavefronts of a SIMD take the two halves of a step in opposite order: one
 // forms the next step's factors while the other feeds the matrix cores.
-// Measured, those 256 ROIs: 1.09 ms per call against 10.5 ms for the whole
+// Measured, those 256 ROIs: 1.11 ms per call against 10.5 ms for the whole
 // grid as one complex GEMM on FP32 MFMA (which ran at 97 % of that unit's
 // rate), and 1.9-2.1 ms for half the grid with complex products on FP16
 // parts; the faces and lines as launches of their own 1.23 ms.  One ROI at
-// L = 64: 0.16 ms (0.57 before), at L = 32 with 130 atoms 26 us (27).  Bound:
-// MFMA (0.39 ms at the peak clock) with the factor and split instructions
-// beside it.
+// L = 64: 0.16 ms (0.57 before), at L = 32 with 130 atoms 26 us (27).  ROIs of
+// a handful of atoms are slower than they were, since a step always forms 32
+// atoms' factors (64 ROIs of 1 atom at L = 64: 29 us, 16 before).  Bound: matrix cores
+// 41 % of the kernel's cycles and the factor and split instructions, 39 %, which
+// overlap only in part.
 #include <math.h>
 
 #include "ar_internal.h"

@@ -16,8 +16,8 @@
 // Membership is decided exactly as the paper's single-precision test:
 // fmaf(dz,dz,fmaf(dy,dy,dx*dx)) <= (float)(R*R).
 //
-// Measured on a tip of 2.8e6 atoms and 8000 ROIs (R = 2 nm): 0.37 ms per call,
-// 0.48 with the sort by global atomics, and 0.97 where one wavefront per ROI
+// Measured on a tip of 2.8e6 atoms and 8000 ROIs (R = 2 nm): 0.34-0.37 ms per
+// call, 0.48 with the sort by global atomics, and 0.97 where one wavefront per ROI
 // walked its bounding cube, a second atomic pass scattered and one thread per
 // cell sorted; 300 ROIs in 1.2e5 atoms 0.09 ms, 0.37.  Bound: the two passes
 // over the ROIs' rows (0.17 ms), then the sort's passes over its records.

@@ -356,11 +356,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, 8))) 
 // Bound: the FFT form kept the LDS busy 81 % of the time at 1024 bins (471
 // cycles per ROI-direction, 115 of them conflicts of the atomics).  Here the
 // histograms are written and read once, and two directions share their words:
-// 179 cycles, the atomics and their conflicts most of it, with the vector unit
-// (235 instructions per ROI-direction, FFT form 393) busy 77 % of the time and
-// now the bound; one direction per word took 249.  200 ROIs of 1006 atoms and
-// 10242 directions: 1.00 ms, one direction per word 1.21, FFT form 2.04; 500
-// clipped ROIs in the persistent form 2.6 ms, 3.14, 5.34.  Three workgroups
+// 179 cycles (85 of them conflicts of the atomics), 66-71 % of the kernel's
+// cycles, and the bound is vector issue: 235 instructions per ROI-direction
+// (FFT form 393) take 88-90 % of them, the matrix cores 12 %.  One direction
+// per word took 249 LDS cycles.  200 ROIs of 1006 atoms and 10242 directions:
+// 0.99 ms, one direction per word 1.21, FFT form 2.04; 500 clipped ROIs in the
+// persistent form 2.56 ms, 3.14, 5.34.  Three workgroups
 // per CU (12-byte atoms in the stage, 168 registers): two cost 9 %, four
 // (spilling) 10 %.  Reading the next atoms ahead of the atomics changed
 // nothing.

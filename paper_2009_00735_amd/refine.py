@@ -20,7 +20,7 @@ class SFScore(torch.autograd.Function):
     Where a gradient will be asked for, the forward pass runs the adjoint
     kernel, which forms J on its way, and keeps dJ/dq for the backward pass:
     one evaluation instead of a score and an adjoint over the same sums
-    (256 ROIs, 10242 directions, 4 frequencies: 2.11 ms against 3.65).  A
+    (256 ROIs, 10242 directions, 4 frequencies: 2.13 ms against 3.68).  A
     forward pass whose gradient is never taken costs 1.4 times the score
     alone; under no_grad, or for quaternions that need no gradient, only the
     score is formed, with the same value.  The inputs are saved as well: a
