@@ -102,6 +102,7 @@ struct ar_context {
 
 struct ar_library {
     ar_context *ctx = nullptr;
+    int device = 0;               // the context may be destroyed before the library
     const float *ref = nullptr;   // caller-owned FP32 raw images [n_lib][K]
     int64_t n_lib = 0;
     int32_t n_win = 0, n_dir = 0;

@@ -959,6 +959,7 @@ ar_status ar_library_create(ar_context *ctx, const float *ref_images, int64_t n_
     auto *lib = new (std::nothrow) ar_library();
     if (!lib) return fail(AR_ENOMEM, "library allocation failed");
     lib->ctx = ctx;
+    lib->device = ctx->device;
     lib->ref = ref_images;
     lib->n_lib = n_lib;
     lib->n_win = n_win;
@@ -1022,7 +1023,7 @@ ar_status ar_library_lookup(const ar_library *lib, const int32_t *idx, int64_t n
     if (n == 0) return AR_OK;
     AR_CHECK(idx != nullptr && (quats || phase), "idx is NULL or no output given");
     AR_CHECK((n + 255) / 256 < (int64_t)INT32_MAX, "too many entries");
-    AR_HIP(hipSetDevice(lib->ctx->device));
+    AR_HIP(hipSetDevice(lib->device));
     idx::k_library_lookup<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
         lib->quats.as<double>(), lib->phase.as<int32_t>(), lib->n_lib, idx, n, quats, phase);
     AR_HIP(hipGetLastError());
@@ -1032,7 +1033,7 @@ ar_status ar_library_lookup(const ar_library *lib, const int32_t *idx, int64_t n
 ar_status ar_library_destroy(ar_library *lib)
 {
     if (!lib) return AR_OK;
-    (void)hipSetDevice(lib->ctx->device);
+    (void)hipSetDevice(lib->device);
     (void)hipDeviceSynchronize();
     delete lib;
     return AR_OK;

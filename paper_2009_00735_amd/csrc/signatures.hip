@@ -728,6 +728,7 @@ ar_status launch_plain(ar_context *ctx, const float *rel, const int64_t *offsets
 // ================================================================== plans
 struct ar_plan {
     ar_context *ctx = nullptr;
+    int device = 0;           // the context may be destroyed before the plan
     int64_t max_roi = 0, max_total = 0;
     int32_t n_dir = 0, nbins = 0, n_win = 0;
     // tuned configuration
@@ -902,6 +903,7 @@ ar_status ar_signature_plan_create(ar_context *ctx, int64_t max_roi, int64_t max
     auto *p = new (std::nothrow) ar_plan();
     if (!p) return ar::fail(AR_ENOMEM, "plan allocation failed");
     p->ctx = ctx;
+    p->device = ctx->device;
     p->max_roi = max_roi;
     p->max_total = max_total;
     p->n_dir = n_dir;
@@ -920,7 +922,7 @@ ar_status ar_signature_plan_create(ar_context *ctx, int64_t max_roi, int64_t max
 ar_status ar_signature_plan_destroy(ar_plan *plan)
 {
     if (!plan) return AR_OK;
-    (void)hipSetDevice(plan->ctx->device);
+    (void)hipSetDevice(plan->device);
     (void)hipDeviceSynchronize();
     delete plan;
     return AR_OK;

@@ -53,6 +53,7 @@
 
 struct ar_sparse_lut {
     ar_context *ctx = nullptr;
+    int device = 0;                      // the context may be destroyed before the table
     int32_t n_phase = 0, n_win = 0, n_dir = 0, n_hat = 0;
     int64_t n_lib = 0;
     int64_t ld = 0;                      // row length of lut_ig (orientations + padding)
@@ -1067,6 +1068,7 @@ ar_status ar_sparse_lut_create(ar_context *ctx, const float *reference, int32_t 
     auto *lut = new (std::nothrow) ar_sparse_lut();
     if (!lut) return fail(AR_ENOMEM, "look-up table allocation failed");
     lut->ctx = ctx;
+    lut->device = ctx->device;
     lut->n_phase = n_phase;
     lut->n_win = n_win;
     lut->n_dir = n_dir;
@@ -1217,7 +1219,7 @@ ar_status ar_sparse_lut_create(ar_context *ctx, const float *reference, int32_t 
 ar_status ar_sparse_lut_destroy(ar_sparse_lut *lut)
 {
     if (!lut) return AR_OK;
-    (void)hipSetDevice(lut->ctx->device);
+    (void)hipSetDevice(lut->device);
     (void)hipDeviceSynchronize();
     delete lut;
     return AR_OK;
@@ -1227,7 +1229,7 @@ ar_status ar_sparse_lut_export(const ar_sparse_lut *lut, int32_t *strong_idx, fl
                                void *stream)
 {
     AR_CHECK(lut != nullptr, "look-up table is NULL");
-    AR_HIP(hipSetDevice(lut->ctx->device));
+    AR_HIP(hipSetDevice(lut->device));
     hipStream_t s = (hipStream_t)stream;
     const size_t nh = (size_t)lut->n_phase * lut->n_hat;
     if (strong_idx)
