@@ -513,11 +513,11 @@ __device__ __forceinline__ void process_item_mm(const float4 *__restrict__ rel, 
             u.load(dirs, v, v1);
             clear_spectra<NB>(x);
         }
-        for (int s0 = 0; s0 < nw; s0 += kSpan) {
-            const int s1 = s0 + min(kSpan, nw - s0);
+        for (uint32_t s0 = 0; s0 < (uint32_t)nw; s0 += kSpan) {
+            const uint32_t s1 = s0 + min((uint32_t)kSpan, nw - s0);
             if (active) zero_hist_mm<NB>(hist, lane);
-            for (int c0 = s0; c0 < s1; c0 += cap) {
-                const int n = min(cap, s1 - c0);
+            for (uint32_t c0 = s0; c0 < s1; c0 += cap) {
+                const int n = (int)min((uint32_t)cap, s1 - c0);
                 __syncthreads();
                 stage_atoms(xs, rel, off0 + c0, n);
                 __syncthreads();
