@@ -260,8 +260,8 @@ __device__ __forceinline__ void process_item(const float4 *__restrict__ rel, int
             vz = dirs[3 * v + 2];
             zero_hist<NB>(A, lane);
         }
-        for (int c0 = 0; c0 < nw; c0 += cap) {
-            const int n = min(cap, nw - c0);
+        for (uint32_t c0 = 0; c0 < (uint32_t)nw; c0 += cap) {
+            const int n = (int)min((uint32_t)cap, nw - c0);
             __syncthreads();
             stage_atoms(xs, rel, off0 + c0, n);
             __syncthreads();
