@@ -557,11 +557,13 @@ static ar_status query(ar_context *ctx, const Grid &g, const float *centres, int
     // 16 wavefronts per ROI where the ROIs alone would not fill the chip
     const unsigned threads = n_roi < 512 ? 1024 : n_roi <= kRowRois ? 256 : 64;
     int32_t *rows = n_roi <= kRowRois ? ctx->g_rows.as<int32_t>() : nullptr;
-    k_roi_query<FILL><<<(unsigned)n_roi, threads, 0, stream>>>(
-        ctx->g_sorted.as<float4>(), ctx->g_cell_start.as<int32_t>(), g, reach, centres, ball2(radius), type_mask,
-        rows, ctx->g_counts.as<int32_t>(), count_out, count_stride, offsets, (float4 *)rel);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    return by_rows(n_roi, threads, [&](int64_t r0, unsigned n) {
+        k_roi_query<FILL><<<n, threads, 0, stream>>>(
+            ctx->g_sorted.as<float4>(), ctx->g_cell_start.as<int32_t>(), g, reach, centres + 3 * r0, ball2(radius),
+            type_mask, rows ? rows + r0 * kRows : rows, ctx->g_counts.as<int32_t>() + r0,
+            count_out ? count_out + r0 * count_stride : count_out, count_stride, offsets ? offsets + r0 : offsets,
+            (float4 *)rel);
+    });
 }
 
 // Offsets of every ROI's rows, their total and the largest ROI (waits for them).

@@ -921,17 +921,20 @@ ar_status run_index(ar_context *ctx, CorrForm form, int64_t rows, const CorrCfg 
     if (waves)
         k_select<CAND><<<(unsigned)n_roi, 64 * (int)std::min<int64_t>(select_waves(CAND), lib->n_pad / 256), 0, s>>>(
             cs, (int)lib->n_pad, merged);
-    else if constexpr (CAND == 64)
-        k_merge64<<<(unsigned)((n_roi + 3) / 4), 256, 0, s>>>(cs, ci, n_lists, n_roi, merged);
     else
-        k_merge<CAND><<<(unsigned)((n_roi + 3) / 4), 256, 0, s>>>(cs, ci, n_lists, n_roi, merged);
+        AR_TRY(by_rows(n_roi, 128, [&](int64_t r0, unsigned n) {
+            const size_t e = (size_t)r0 * n_lists * CAND;
+            const unsigned grid = (unsigned)(((int64_t)n + 3) / 4);
+            if constexpr (CAND == 64) k_merge64<<<grid, 256, 0, s>>>(cs + e, ci + e, n_lists, n, merged + r0 * CAND);
+            else k_merge<CAND><<<grid, 256, 0, s>>>(cs + e, ci + e, n_lists, n, merged + r0 * CAND);
+        }));
     AR_HIP(hipGetLastError());
     AR_TRY(launch_rescore<CAND>(ctx, images, lib, n_roi, k, top_idx, top_score, s));
-    if (cand_idx) {
-        const int64_t n = n_roi * CAND;
-        k_copy_cand<CAND><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(merged, n_roi, cand_idx);
-        AR_HIP(hipGetLastError());
-    }
+    if (cand_idx)
+        AR_TRY(by_rows(n_roi, 2 * CAND, [&](int64_t r0, unsigned n) {
+            k_copy_cand<CAND><<<(unsigned)(((int64_t)n * CAND + 255) / 256), 256, 0, s>>>(merged + r0 * CAND, n,
+                                                                                         cand_idx + r0 * CAND);
+        }));
     return AR_OK;
 }
 
@@ -973,12 +976,11 @@ ar_status ar_library_create(ar_context *ctx, const float *ref_images, int64_t n_
     if (st == AR_OK)
         st = idx::normalise_cast(ref_images, n_lib, lib->n_pad, n_win, n_dir, lib->Kp, lib->inv_max.as<float>(),
                                  lib->bf16.as<uint16_t>(), s);
-    if (st == AR_OK) {
-        idx::k_row_norm2<<<(unsigned)lib->n_pad, 256, 0, s>>>(lib->bf16.as<uint16_t>(), lib->Kp, n_lib,
-                                                              lib->norm2.as<float>());
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) st = fail(AR_EDEVICE, "k_row_norm2: %s", hipGetErrorString(e));
-    }
+    if (st == AR_OK)
+        st = by_rows(lib->n_pad, 256, [&](int64_t r0, unsigned n) {
+            idx::k_row_norm2<<<n, 256, 0, s>>>(lib->bf16.as<uint16_t>() + (size_t)r0 * lib->Kp, lib->Kp, n_lib - r0,
+                                               lib->norm2.as<float>() + r0);
+        });
     if (st != AR_OK) {
         delete lib;
         return st;
@@ -1024,10 +1026,11 @@ ar_status ar_library_lookup(const ar_library *lib, const int32_t *idx, int64_t n
     AR_CHECK(idx != nullptr && (quats || phase), "idx is NULL or no output given");
     AR_CHECK((n + 255) / 256 < (int64_t)INT32_MAX, "too many entries");
     AR_HIP(hipSetDevice(lib->device));
-    idx::k_library_lookup<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
-        lib->quats.as<double>(), lib->phase.as<int32_t>(), lib->n_lib, idx, n, quats, phase);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    return by_rows(n, 2, [&](int64_t i0, unsigned m) {
+        idx::k_library_lookup<<<(unsigned)(((int64_t)m + 255) / 256), 256, 0, (hipStream_t)stream>>>(
+            lib->quats.as<double>(), lib->phase.as<int32_t>(), lib->n_lib, idx + i0, m, quats ? quats + 4 * i0 : quats,
+            phase ? phase + i0 : phase);
+    });
 }
 
 ar_status ar_library_destroy(ar_library *lib)

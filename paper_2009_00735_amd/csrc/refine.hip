@@ -761,10 +761,12 @@ static ar_status sf_launch_ws(int mode, const float *rel, const int64_t *offsets
                                    rep, mate, n_eval, n_tiles, freqs, targets, p, a);
     }));
     if (mode == 2) return AR_OK;
-    sf::k_sf_reduce<<<(unsigned)((n_roi + 15) / 16), 256, 0, s>>>(part, n_tiles, n_roi, quats, score,
-                                                                    mode == 1 ? grad : nullptr);
-    AR_HIP(hipGetLastError());
-    return AR_OK;
+    if (mode == 0) grad = nullptr;
+    return by_rows(n_roi, 32, [&](int64_t r0, unsigned n) {
+        sf::k_sf_reduce<<<(unsigned)(((int64_t)n + 15) / 16), 256, 0, s>>>(
+            part + (size_t)r0 * n_tiles * sf::kPartial, n_tiles, n, quats + 4 * r0, score ? score + r0 : score,
+            grad ? grad + 4 * r0 : grad);
+    });
 }
 
 // One evaluation with the context's (growable) workspace.

@@ -79,16 +79,17 @@ __global__ __launch_bounds__(256) void k_keep(const float *__restrict__ I, const
     flag[r] = keep;
 }
 
-// one thread per (ROI, sub-cell); kept ROI r writes s^3 rows from pos[r] s^3
+// one thread per (ROI, sub-cell) of the n_roi ROIs from r0 on; kept ROI r writes
+// s^3 rows from pos[r] s^3
 __global__ __launch_bounds__(256) void k_emit(const float *__restrict__ centres, const int32_t *__restrict__ flag,
-                                              const int64_t *__restrict__ pos, int64_t n_roi, int split,
+                                              const int64_t *__restrict__ pos, int64_t r0, int64_t n_roi, int split,
                                               Offsets off, float *__restrict__ out, int32_t *__restrict__ parent)
 {
     const int s3 = split * split * split;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t r = t / s3;
-    if (r >= n_roi || !flag[r]) return;
-    const int c = (int)(t - r * s3);
+    const int64_t r = r0 + t / s3;
+    if (t >= n_roi * s3 || !flag[r]) return;
+    const int c = (int)(t % s3);
     const int i = c / (split * split), j = (c / split) % split, k = c % split;
     const int64_t o = pos[r] * s3 + c;
     out[3 * o] = centres[3 * r] + off.d[i];
@@ -125,8 +126,10 @@ extern "C" ar_status ar_refine_roi_grid(ar_context *ctx, const float *centres, c
     AR_TRY(pos.reserve(sizeof(int64_t) * (n_roi + 1)));
     AR_TRY(temp.reserve(sizeof(int64_t) * ar::scan::tiles(n_roi) + 16));
 
-    k_intensity<<<(unsigned)n_roi, 256, 0, s>>>(images, counts, n_win, n_dir, I.as<float>());
-    AR_HIP(hipGetLastError());
+    AR_TRY(ar::by_rows(n_roi, 256, [&](int64_t r0, unsigned n) {
+        k_intensity<<<n, 256, 0, s>>>(images + (size_t)r0 * n_win * n_dir, counts + r0, n_win, n_dir,
+                                      I.as<float>() + r0 * n_win);
+    }));
     k_best<<<(unsigned)n_win, 1024, 0, s>>>(I.as<float>(), n_roi, n_win, best.as<float>());
     AR_HIP(hipGetLastError());
     k_keep<<<(unsigned)((n_roi + 255) / 256), 256, 0, s>>>(I.as<float>(), best.as<float>(), n_roi, n_win, window_mask,
@@ -149,9 +152,10 @@ extern "C" ar_status ar_refine_roi_grid(ar_context *ctx, const float *centres, c
         off.d[i] = i < split ? (float)((double)h * (double)(2 * i + 1 - split) / (double)(2 * split)) : 0.0f;
     const int64_t threads = n_roi * s3;
     AR_CHECK((threads + 255) / 256 < (int64_t)INT32_MAX, "too many ROIs");
-    k_emit<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(centres, flag.as<int32_t>(), pos.as<int64_t>(), n_roi,
-                                                             split, off, out_centres, out_parent);
-    AR_HIP(hipGetLastError());
+    AR_TRY(ar::by_rows(n_roi, 2 * s3, [&](int64_t r0, unsigned n) {
+        k_emit<<<(unsigned)((n * s3 + 255) / 256), 256, 0, s>>>(centres, flag.as<int32_t>(), pos.as<int64_t>(), r0, n,
+                                                                split, off, out_centres, out_parent);
+    }));
     // the local buffers are freed on return; hipFree waits for the kernels
     return AR_OK;
 }

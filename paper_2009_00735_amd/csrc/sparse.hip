@@ -320,12 +320,12 @@ __global__ __launch_bounds__(256) void k_sparse_lut(const double *__restrict__ q
 __global__ __launch_bounds__(256) void k_lut_rows(const uint16_t *__restrict__ lut_ig, int64_t ld,
                                                   const int32_t *__restrict__ kpos, const int32_t *__restrict__ kcmp,
                                                   const int64_t *__restrict__ phase_start, int n_phase,
-                                                  int64_t n_lib, int n_hat, uint16_t *__restrict__ lut_gi)
+                                                  int64_t g0, int64_t n, int n_hat, uint16_t *__restrict__ lut_gi)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= n_lib * n_hat) return;
-    const int64_t g = t / n_hat;
-    const int i = (int)(t - g * n_hat);
+    if (t >= n * n_hat) return;
+    const int64_t g = g0 + t / n_hat;
+    const int i = (int)(t % n_hat);
     const int c = phase_of(g, phase_start, n_phase);
     lut_gi[(size_t)g * n_hat + kcmp[(size_t)c * n_hat + i]] = lut_ig[(size_t)kpos[(size_t)c * n_hat + i] * ld + g];
 }
@@ -334,14 +334,14 @@ __global__ __launch_bounds__(256) void k_lut_rows(const uint16_t *__restrict__ l
 __global__ __launch_bounds__(256) void k_lut_export(const uint16_t *__restrict__ lut_gi,
                                                     const int32_t *__restrict__ kcmp,
                                                     const int64_t *__restrict__ phase_start, int n_phase,
-                                                    int64_t n_lib, int n_hat, int32_t *__restrict__ out)
+                                                    int64_t g0, int64_t n, int n_hat, int32_t *__restrict__ out)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= n_lib * n_hat) return;
-    const int64_t g = t / n_hat;
-    const int i = (int)(t - g * n_hat);
+    if (t >= n * n_hat) return;
+    const int64_t g = g0 + t / n_hat;
+    const int i = (int)(t % n_hat);
     const int c = phase_of(g, phase_start, n_phase);
-    out[t] = lut_gi[(size_t)g * n_hat + kcmp[(size_t)c * n_hat + i]];
+    out[(size_t)g * n_hat + i] = lut_gi[(size_t)g * n_hat + kcmp[(size_t)c * n_hat + i]];
 }
 
 // ------------------------------------------------------------ indexing
@@ -1181,9 +1181,10 @@ ar_status ar_sparse_lut_create(ar_context *ctx, const float *reference, int32_t 
     }
     if (st == AR_OK) {
         const int64_t n = (int64_t)n_rows * lut->ld;   // padding rows and columns: the zero node
-        sparse::k_fill_u16<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(lut->lut_ig.as<uint16_t>(), n,
-                                                                       (uint16_t)n_dir);
-        launched("k_fill_u16");
+        step(by_rows(n, 2, [&](int64_t i0, unsigned m) {
+            sparse::k_fill_u16<<<(unsigned)(((int64_t)m + 255) / 256), 256, 0, s>>>(lut->lut_ig.as<uint16_t>() + i0, m,
+                                                                                   (uint16_t)n_dir);
+        }));
     }
     if (st == AR_OK) {
         sparse::k_window_order<<<dim3((unsigned)((n_hat + 255) / 256), (unsigned)n_phase), 256, 0, s>>>(
@@ -1200,13 +1201,12 @@ ar_status ar_sparse_lut_create(ar_context *ctx, const float *reference, int32_t 
             lut->kpos.as<int32_t>(), n_hat, directions, n_dir, mc, lut->lut_ig.as<uint16_t>(), lut->ld);
         launched("k_sparse_lut");
     }
-    if (st == AR_OK) {
-        const int64_t n = n_lib * n_hat;
-        sparse::k_lut_rows<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
-            lut->lut_ig.as<uint16_t>(), lut->ld, lut->kpos.as<int32_t>(), lut->kcmp.as<int32_t>(),
-            lut->phase_start.as<int64_t>(), n_phase, n_lib, n_hat, lut->lut_gi.as<uint16_t>());
-        launched("k_lut_rows");
-    }
+    if (st == AR_OK)
+        step(by_rows(n_lib, 2 * (int64_t)n_hat, [&](int64_t g0, unsigned n) {
+            sparse::k_lut_rows<<<(unsigned)(((int64_t)n * n_hat + 255) / 256), 256, 0, s>>>(
+                lut->lut_ig.as<uint16_t>(), lut->ld, lut->kpos.as<int32_t>(), lut->kcmp.as<int32_t>(),
+                lut->phase_start.as<int64_t>(), n_phase, g0, n, n_hat, lut->lut_gi.as<uint16_t>());
+        }));
     // ref_max is freed on return: hipFree waits for the kernels that read it
     if (st != AR_OK) {
         delete lut;
@@ -1236,14 +1236,12 @@ ar_status ar_sparse_lut_export(const ar_sparse_lut *lut, int32_t *strong_idx, fl
         AR_HIP(hipMemcpyAsync(strong_idx, lut->strong_idx.ptr, sizeof(int32_t) * nh, hipMemcpyDeviceToDevice, s));
     if (strong_val)
         AR_HIP(hipMemcpyAsync(strong_val, lut->strong_val.ptr, sizeof(float) * nh, hipMemcpyDeviceToDevice, s));
-    if (nodes) {
-        const int64_t n = lut->n_lib * lut->n_hat;
-        sparse::k_lut_export<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
-            lut->lut_gi.as<uint16_t>(), lut->kcmp.as<int32_t>(), lut->phase_start.as<int64_t>(), lut->n_phase,
-            lut->n_lib, lut->n_hat, nodes);
-        AR_HIP(hipGetLastError());
-    }
-    return AR_OK;
+    if (!nodes) return AR_OK;
+    return by_rows(lut->n_lib, 2 * (int64_t)lut->n_hat, [&](int64_t g0, unsigned n) {
+        sparse::k_lut_export<<<(unsigned)(((int64_t)n * lut->n_hat + 255) / 256), 256, 0, s>>>(
+            lut->lut_gi.as<uint16_t>(), lut->kcmp.as<int32_t>(), lut->phase_start.as<int64_t>(), lut->n_phase, g0, n,
+            lut->n_hat, nodes);
+    });
 }
 
 ar_status ar_sparse_lut_screen(const ar_sparse_lut *lut, int32_t *rois_per_read)
